@@ -100,6 +100,22 @@ __device__ __forceinline__ float wave_max(float v) {
     return fmaxf(fmaxf(lane_f32(v, 0), lane_f32(v, 16)), fmaxf(lane_f32(v, 32), lane_f32(v, 48)));
 }
 
+// Sum and maximum over the four lanes l, l ^ 16, l ^ 32, l ^ 48 by register swaps (v_permlane16_swap
+// exchanges odd rows of one operand with even rows of the other, v_permlane32_swap halves): every
+// lane ends with (r0 + r1) + (r2 + r3) of its column.
+__device__ __forceinline__ float quad_rows_sum(float s) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+    s = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
+__device__ __forceinline__ float quad_rows_max(float s) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+    s = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+
 // Block-wide sum of 256 threads in a fixed order: butterfly inside each wave, then waves 0..3.
 __device__ __forceinline__ float block_sum256(float v, float *lds4) {
     v = wave_sum(v);
@@ -217,6 +233,33 @@ __device__ __forceinline__ uint4 pack_frag(const float *v) {
         return uint4{w[0], w[1], w[2], w[3]};
     }
     return uint4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+}
+
+// Two floats to bf16 (round to nearest even, the hardware's packed conversion), the first in the low
+// half; and a 16-byte fragment of EPL floats by it, and back.
+__device__ __forceinline__ uint32_t pack2bf(float lo, float hi) {
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    const bf16x2 v = {(__bf16)lo, (__bf16)hi};
+    return __builtin_bit_cast(uint32_t, v);
+}
+template <DType T>
+__device__ __forceinline__ uint4 pack_frag_cvt(const float *v) {
+    if (T == DType::BF16)
+        return uint4{pack2bf(v[0], v[1]), pack2bf(v[2], v[3]), pack2bf(v[4], v[5]), pack2bf(v[6], v[7])};
+    return uint4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+}
+template <DType T>
+__device__ __forceinline__ void unpack_frag(const uint4 &f, float *v) {
+    const uint32_t w[4] = {f.x, f.y, f.z, f.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (T == DType::BF16) {
+            v[2 * k] = __uint_as_float(w[k] << 16);
+            v[2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u);
+        } else {
+            v[k] = __uint_as_float(w[k]);
+        }
+    }
 }
 
 // Zero the elements of a 16-byte value fragment whose key index (first + e) is >= limit.

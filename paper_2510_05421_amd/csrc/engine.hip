@@ -77,6 +77,7 @@ struct dvi_ctx {
     // GEMM inputs (hg, act, attn_o, hk_hg, dfm, pfm, ufm) are in the fragment-major layout.
     float *h, *ss, *q, *hk, *hk_ss, *vlogits, *dlogits, *lora_u;
     float *sinv_rows;  // 1/rms per token for prefill-block GEMMs
+    int2 *rowmap;      // (sequence, position) of a prefill block's rows
     int chunk_stride = 0;  // 64-key chunks of the longest sequence (max_seq), the attention grid's cap
     void *hg, *attn_o, *act, *hk_hg, *hk_hat, *dfm, *pfm, *ufm;
     // scratch in the workspace (ws_scr), and the scratch the launches use (scr): ws_scr, except
@@ -188,11 +189,13 @@ static int m_max(const dvi_config &c) {
     int m = c.max_batch * c.max_k_spec;
     return m > kMaxRows ? m : kMaxRows;
 }
-// Rows of one prefill block (batch x prompt positions).  Prefill attention keeps no partials, so
-// the block is bounded by its activations only.
+// Rows of one prefill block: up to 8192 of the prompts' rows laid end to end.  Prefill attention keeps
+// no partials, so a block is bounded by its activations only (72 KiB a row at the 7B shape).  Larger
+// blocks leave the many-row GEMMs fewer partly filled rounds of tiles (7B layer, 8192 rows: 2.79 ms
+// as four blocks of 2048, 2.64 ms as one); a context never has more rows than its batch of prompts.
 static int prefill_rows(const dvi_config &c) {
-    const int mm = m_max(c);
-    return 2048 > mm ? 2048 : mm;
+    const size_t most = (size_t)c.max_batch * c.max_seq, mm = m_max(c);
+    return (int)std::max(mm, std::min(most, (size_t)8192));
 }
 // Bytes of the split-KV attention partials of a decode step (outputs and statistics of every
 // 64-key chunk of m_max rows); they are addressed with 32-bit byte offsets.
@@ -235,6 +238,7 @@ static size_t layout(dvi_ctx *x, const dvi_config &c, void *base) {
     void *attn_o = b.take<void>(Mp16 * qd * es);
     void *act = b.take<void>(Mp16 * F * es);
     float *sinv_rows = b.take<float>(Mp * 4);
+    int2 *rowmap = b.take<int2>(Mp * 8);
     float *hk = b.take<float>(Bk * d * 4);
     float *hk_ss = b.take<float>(Bk * nps * 4);
     void *hk_hg = b.take<void>(Bk16 * d * es);
@@ -266,7 +270,8 @@ static size_t layout(dvi_ctx *x, const dvi_config &c, void *base) {
     int32_t *targets = b.take<int32_t>(Bk * 4);
     int32_t *forced = b.take<int32_t>(Bk * 4);
     int32_t *max_new = b.take<int32_t>(c.max_batch * 4);
-    int32_t *ids = b.take<int32_t>((size_t)c.max_batch * c.max_seq * 4);
+    // the prompts' ids end to end, then where each sequence starts
+    int32_t *ids = b.take<int32_t>(((size_t)c.max_batch * c.max_seq + c.max_batch + 1) * 4);
     int32_t *copy_list = b.take<int32_t>((1 + 2 * Bk) * 4);
     int32_t *ring_state = b.take<int32_t>(4 * 4);
     int32_t *rng_step = b.take<int32_t>(4 * 4);
@@ -297,7 +302,7 @@ static size_t layout(dvi_ctx *x, const dvi_config &c, void *base) {
     if (x && base) {
         x->L = Ls;
         x->emb = emb; x->head = head; x->final_norm = final_norm; x->rope = rope;
-        x->h = h; x->ss = ss; x->hg = hg; x->q = q; x->attn_o = attn_o; x->act = act; x->sinv_rows = sinv_rows;
+        x->h = h; x->ss = ss; x->hg = hg; x->q = q; x->attn_o = attn_o; x->act = act; x->sinv_rows = sinv_rows; x->rowmap = rowmap;
         x->hk = hk; x->hk_ss = hk_ss; x->hk_hg = hk_hg; x->hk_hat = hk_hat;
         x->dfm = dfm; x->pfm = pfm; x->ufm = ufm;
         x->vlogits = vlogits; x->dlogits = dlogits;
@@ -556,7 +561,9 @@ static void gemm(dvi_ctx *x, Epi e, int cls, const void *W, const void *X, int M
     a.sinv_rows = x->sinv_rows;
     a.kpart = x->scr.kpart;
     const LaunchEvents ev = probe_begin(x, cls);
-    if (!launch_gemm(x->dt, e, a, x->stream, ev))
+    if (a.rowmap != nullptr)
+        launch_gemm_rows(x->dt, e, a, x->stream, ev);
+    else if (!launch_gemm(x->dt, e, a, x->stream, ev))
         (void)fail(x, DVI_ERR_DEVICE, "no GEMM variant for %d rows of epilogue %d", M, (int)e);
     probe_end(x, ev, gemm_bytes(x, e, M, N, K));
 }
@@ -587,7 +594,7 @@ static int max_len(const dvi_ctx *x) {
 }
 
 static dvi_status run_layers(dvi_ctx *x, int l0, int l1, int B, int c, int pos_off, int n_chunks, float *h, float *ss,
-                             void *hg, int rs, void *out_hg, int out_rs, int out_off, bool prefill = false) {
+                             void *hg, int rs, void *out_hg, int out_rs, int out_off) {
     const dvi_config &cf = x->cfg;
     const int d = cf.d_model, F = cf.ffn_dim, H = cf.n_heads, Hkv = cf.n_kv_heads, hd = cf.head_dim;
     const int nps = d / 16;
@@ -595,7 +602,6 @@ static dvi_status run_layers(dvi_ctx *x, int l0, int l1, int B, int c, int pos_o
     for (int l = l0; l < l1; ++l) {
         const LayerW &Lw = x->L[l];
         GemmArgs a{};
-        a.large_m = prefill;
         a.ss_in = ss;
         a.ld_ss_in = rs * nps;
         a.eps = cf.rms_eps;
@@ -630,7 +636,6 @@ static dvi_status run_layers(dvi_ctx *x, int l0, int l1, int B, int c, int pos_o
         at.part_ml = x->scr.att_pml;
         at.counters = x->scr.att_cnt;
         at.O = x->attn_o;
-        at.flash = prefill ? 1 : 0;
         const LaunchEvents ev = probe_begin(x, DVI_PROBE_ATTENTION);
         launch_attention(x->dt, at, x->stream, ev);
         if (ev.start) {
@@ -640,7 +645,6 @@ static dvi_status run_layers(dvi_ctx *x, int l0, int l1, int B, int c, int pos_o
             probe_end(x, ev, kv + (double)M * H * hd * (4.0 + x->es));
         }
         GemmArgs r{};
-        r.large_m = prefill;
         r.H = h;
         r.ldh = rs * d;
         r.ss_out = ss;
@@ -651,7 +655,6 @@ static dvi_status run_layers(dvi_ctx *x, int l0, int l1, int B, int c, int pos_o
         r.g_next = Lw.mlp_norm;
         gemm(x, EPI_RESID, DVI_PROBE_ATTN_OUT, Lw.wo, x->attn_o, M, d, H * hd, r);
         GemmArgs g{};
-        g.large_m = prefill;
         g.ss_in = ss;
         g.ld_ss_in = rs * nps;
         g.eps = cf.rms_eps;
@@ -663,6 +666,62 @@ static dvi_status run_layers(dvi_ctx *x, int l0, int l1, int B, int c, int pos_o
             r.hg_rs = out_rs;
             r.hg_off = out_off;
         }
+        gemm(x, EPI_RESID, DVI_PROBE_DOWN, Lw.wd, x->act, M, d, F, r);
+    }
+    LAUNCHCHK(x);
+    return DVI_OK;
+}
+
+// All layers on a prefill block of M rows (rows of h / ss / hg, positions in rowmap; runs in at).
+static dvi_status run_prefill_layers(dvi_ctx *x, int M, FlashArgs at) {
+    const dvi_config &cf = x->cfg;
+    const int d = cf.d_model, F = cf.ffn_dim, H = cf.n_heads, hd = cf.head_dim, nps = d / 16;
+    at.Q = x->q;
+    at.n_heads = H;
+    at.n_kv = cf.n_kv_heads;
+    at.hd = hd;
+    at.s_max = x->s_cap;
+    at.scale = 1.0f / sqrtf((float)hd);
+    at.O = x->attn_o;
+    for (int l = 0; l < cf.n_layers; ++l) {
+        const LayerW &Lw = x->L[l];
+        GemmArgs a{};
+        a.rowmap = x->rowmap;
+        a.ss_in = x->ss;
+        a.ld_ss_in = nps;
+        a.eps = cf.rms_eps;
+        a.Q = x->q;
+        a.Kc = Lw.Kc;
+        a.Vc = Lw.Vc;
+        a.n_heads = H;
+        a.n_kv = cf.n_kv_heads;
+        a.hd = hd;
+        a.s_max = x->s_cap;
+        a.rope = x->rope;
+        a.A = x->act;
+        gemm(x, EPI_QKV, DVI_PROBE_QKV, Lw.wqkv, x->hg, M, qkv_rows(cf), d, a);
+        at.Kc = Lw.Kc;
+        at.Vc = Lw.Vc;
+        const LaunchEvents ev = probe_begin(x, DVI_PROBE_ATTENTION);
+        launch_flash_prefill(x->dt, at, x->stream, ev);
+        if (ev.start) {
+            double kv = 0.0;  // keys and values up to each run's last position, once per kv head
+            for (int i = 0; i < at.n_seg; ++i)
+                kv += (double)(at.seg_pos[i] + at.seg_len[i]) * cf.n_kv_heads * hd * 2.0 * x->es;
+            probe_end(x, ev, kv + (double)M * H * hd * (4.0 + x->es));
+        }
+        GemmArgs r{};
+        r.rowmap = x->rowmap;
+        r.H = x->h;
+        r.ldh = d;
+        r.ss_out = x->ss;
+        r.ld_ss_out = nps;
+        r.hg_out = x->hg;
+        r.hg_rs = 1;
+        r.g_next = Lw.mlp_norm;
+        gemm(x, EPI_RESID, DVI_PROBE_ATTN_OUT, Lw.wo, x->attn_o, M, d, H * hd, r);
+        gemm(x, EPI_SWIGLU, DVI_PROBE_GATE_UP, Lw.wgu, x->hg, M, 2 * F, d, a);
+        r.g_next = next_gain(x, l);
         gemm(x, EPI_RESID, DVI_PROBE_DOWN, Lw.wd, x->act, M, d, F, r);
     }
     LAUNCHCHK(x);
@@ -775,24 +834,26 @@ extern "C" dvi_status dvi_prefill(dvi_ctx *x, int32_t batch, const int32_t *ids,
     if (!ids || !lens || !first_tok) return fail(x, DVI_ERR_ARG, "null argument");
     if (batch < 1) return fail(x, DVI_ERR_ARG, "batch < 1");
     if (batch > cf.max_batch) return fail(x, DVI_ERR_CAPACITY, "batch %d > max_batch %d", batch, cf.max_batch);
-    // Prompts may differ in length: every sequence runs over P = the longest prompt, the shorter
-    // ones padded with token 0 at the end.  A row attends only to positions at or before its own,
-    // so padding changes no real row; its keys and values lie past the sequence's length, where
-    // decoding overwrites them before any row can read them.
-    int P = 0;
+    // Prompts may differ in length: their rows are laid end to end and run in blocks, each row at its
+    // own sequence and position, so nothing is computed for padding.
+    int T = 0;
     for (int b = 0; b < batch; ++b) {
         if (lens[b] < 1 || lens[b] > stride) return fail(x, DVI_ERR_ARG, "prompt length %d of sequence %d outside [1, stride]", lens[b], b);
         if (lens[b] + 1 > cf.max_seq)
             return fail(x, DVI_ERR_CAPACITY, "prompt length %d leaves no room in max_seq %d", lens[b], cf.max_seq);
-        P = lens[b] > P ? lens[b] : P;
+        T += lens[b];
     }
-    std::vector<int32_t> packed((size_t)batch * P, 0);
+    std::vector<int32_t> packed;
+    packed.reserve((size_t)T + batch + 1);
     for (int b = 0; b < batch; ++b)
         for (int i = 0; i < lens[b]; ++i) {
             const int32_t t = ids[(size_t)b * stride + i];
             if (t < 0 || t >= cf.vocab) return fail(x, DVI_ERR_ARG, "token id %d out of range", t);
-            packed[(size_t)b * P + i] = t;
+            packed.push_back(t);
         }
+    std::vector<int32_t> starts(batch + 1, 0);
+    for (int b = 0; b < batch; ++b) starts[b + 1] = starts[b] + lens[b];
+    packed.insert(packed.end(), starts.begin(), starts.end());
     const int d = cf.d_model;
     HIPCHK(x, hipMemcpyAsync(x->ids, packed.data(), packed.size() * 4, hipMemcpyHostToDevice, x->stream));
     HIPCHK(x, hipMemsetAsync(x->lens, 0, cf.max_batch * 4, x->stream));
@@ -800,26 +861,33 @@ extern "C" dvi_status dvi_prefill(dvi_ctx *x, int32_t batch, const int32_t *ids,
     HIPCHK(x, hipMemsetAsync(flags_ptr(x), 0, 16, x->stream));
     x->B = batch;
     for (int b = 0; b < cf.max_batch; ++b) x->lens_h[b] = 0;
-    const int c = (prefill_rows(cf) / batch) < 1 ? 1 : prefill_rows(cf) / batch;  // positions per block
-    const int nps = d / 16;
-    for (int s0 = 0; s0 < P; s0 += c) {
-        const int cc = (P - s0) < c ? P - s0 : c;
-        launch_embed(x->dt, x->emb, x->ids + s0, P, batch, cc, d, x->h, d, x->ss, nps, x->hg, x->L[0].attn_norm,
-                     x->stream);
-        dvi_status st =
-            run_layers(x, 0, cf.n_layers, batch, cc, s0, attn_chunks(x, s0 + cc - 1), x->h, x->ss, x->hg, 1, x->hg, 1, 0,
-                       true);
-        if (st != DVI_OK) return st;
-        // each sequence's last prompt token -> its first generated token: collect the head's
-        // input rows (pfm, with their sums of squares in hk_ss) from the block that holds them
+    const int rows = prefill_rows(cf), nps = d / 16;
+    for (int t0 = 0; t0 < T; t0 += rows) {
+        const int M = std::min(T - t0, rows);
+        launch_embed_rows(x->dt, x->emb, x->ids, x->ids + T, batch, t0, M, d, x->h, x->ss, x->hg, x->L[0].attn_norm,
+                          x->rowmap, x->stream);
+        // the block's runs of consecutive positions, and the rows that end a prompt: those are the
+        // head's inputs (pfm, with their sums of squares in hk_ss)
+        FlashArgs at{};
         LastRows lr;
+        for (int b = 0; b < kMaxBatch; ++b) lr.src[b] = -1;
         bool any = false;
-        for (int b = 0; b < kMaxBatch; ++b) {
-            const int i = b < batch ? lens[b] - 1 - s0 : -1;
-            lr.src[b] = (i >= 0 && i < cc) ? i : -1;
-            any = any || lr.src[b] >= 0;
+        for (int b = 0; b < batch; ++b) {
+            const int lo = std::max(t0, starts[b]), hi = std::min(t0 + M, starts[b + 1]);
+            if (lo >= hi) continue;
+            const int i = at.n_seg++;
+            at.seg_b[i] = b;
+            at.seg_pos[i] = lo - starts[b];
+            at.seg_row[i] = lo - t0;
+            at.seg_len[i] = hi - lo;
+            if (hi == starts[b + 1]) {
+                lr.src[b] = hi - 1 - t0;
+                any = true;
+            }
         }
-        if (any) launch_gather_last(x->dt, x->hg, x->ss, cc, d, nps, batch, lr, x->pfm, x->hk_ss, x->stream);
+        const dvi_status st = run_prefill_layers(x, M, at);
+        if (st != DVI_OK) return st;
+        if (any) launch_gather_last(x->dt, x->hg, x->ss, d, nps, batch, lr, x->pfm, x->hk_ss, x->stream);
     }
     head(x, x->pfm, x->hk_ss, nps, batch, x->vlogits, false, x->pending, 1, nullptr);
     std::vector<int32_t> lh(cf.max_batch, 0);
@@ -1198,8 +1266,6 @@ extern "C" dvi_status dvi_update_drafter(dvi_ctx *x, const dvi_update_args *ua, 
     u.Bm = x->lora_B;
     u.u = x->upd_u;
     u.Z = x->upd_Z;
-    u.part_val = x->ws_scr.part_val;
-    u.part_idx = x->ws_scr.part_idx;
     u.row_stats = x->upd_stats;
     u.dA = x->upd_dA;
     u.du = x->upd_du;

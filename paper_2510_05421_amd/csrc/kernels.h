@@ -90,11 +90,10 @@ struct GemmArgs {
     float gamma;
     float *part_val;    // [M][N/16]
     int32_t *part_idx;  // [M][N/16]
-    // Large-M GEMM: taken for M > 64, and for any M when large_m is set (every prefill block,
-    // so a prompt's arithmetic never depends on the batch); sinv_rows is its scratch for 1/rms
-    // of every token [M]
-    int large_m;
+    // many-row GEMM (launch_gemm_rows): scratch for 1/rms of every token [M], and, for EPI_QKV, each
+    // row's (sequence, position) instead of c, pos_off and lens
     float *sinv_rows;
+    const int2 *rowmap;
     // Sampled drafting (EPI_LOGITS): when sample_tau > 0 the argmax partials rank
     // z / sample_tau + g, g = -log(-log(u)), u from Philox4x64-10 with key (seed, 0) and counter
     // (n / 4, m * rng_row_stride + rng_row0, *rng_step, 0); Z keeps z itself.
@@ -115,10 +114,13 @@ struct LaunchEvents {
     hipEvent_t start = nullptr, stop = nullptr;
 };
 
-// M <= 64: the weight-streaming decode GEMM.  M > 64 or large_m (prefill blocks): the large-M
-// GEMM, which needs sinv_rows when ss_in is set and takes every epilogue but EPI_LOGITS
-// (returns false).  Each kernel's arithmetic per output is independent of M.
+// The weight-streaming decode GEMM, M <= 64 (returns false for more).  Its arithmetic per output is
+// independent of M.
 bool launch_gemm(DType t, Epi e, const GemmArgs &a, hipStream_t s, const LaunchEvents &ev = {});
+// The many-row GEMM, any M (prefill blocks; the drafter update's logits, EPI_LOGITS with the LoRA term
+// and neither argmax partials nor sampling).  Its arithmetic per output is independent of M too, but
+// not the decode GEMM's.
+void launch_gemm_rows(DType t, Epi e, const GemmArgs &a, hipStream_t s, const LaunchEvents &ev = {});
 // Bytes of GemmArgs::kpart for an N x K matrix (64 tokens); 0 when that matrix never splits.
 size_t gemm_split_bytes(DType t, int N, int K);
 
@@ -138,16 +140,34 @@ void launch_gather_fm(DType t, const void *src, bool src_fm, int rs, int off, in
 
 constexpr int kMaxBatch = 64;
 
-// Rows of one prefill block that hold a sequence's last prompt token: src[b] = the row within
-// the block of sequence b's last token (row b * block_len + src[b]), or -1 when that token lies in
-// another block.
+// The rows of a prefill block, M rows from row t0 of the prompts laid end to end (ids; sequence b's
+// rows start at starts[b], b < B): rowmap[m] = (sequence, position), h, ss and hg (FM) as launch_embed.
+void launch_embed_rows(DType t, const void *emb, const int32_t *ids, const int32_t *starts, int B, int t0, int M, int d,
+                       float *h, float *ss, void *hg, const float *g, int2 *rowmap, hipStream_t s);
+
+// Rows of one prefill block that hold a sequence's last prompt token: src[b] = sequence b's row
+// within the block, or -1 when its last token lies in another block.
 struct LastRows {
     int32_t src[kMaxBatch];
 };
-// For every sequence b with src[b] >= 0: FM row b of dst <- FM row (b * block_len + src[b]) of
-// hg (K = d columns), and row b of ss_dst <- that row of ss (nps partial sums each).
-void launch_gather_last(DType t, const void *hg, const float *ss, int block_len, int d, int nps, int B,
-                        const LastRows &lr, void *dst, float *ss_dst, hipStream_t s);
+// For every sequence b with src[b] >= 0: FM row b of dst <- FM row src[b] of hg (K = d columns), and
+// row b of ss_dst <- that row of ss (nps partial sums each).
+void launch_gather_last(DType t, const void *hg, const float *ss, int d, int nps, int B, const LastRows &lr, void *dst,
+                        float *ss_dst, hipStream_t s);
+
+// Causal attention of a prefill block: the block's rows are n_seg runs of consecutive positions, run i
+// being rows seg_row[i] .. + seg_len[i] of sequence seg_b[i] from position seg_pos[i] on.  Every row
+// attends to the cache positions up to its own.
+struct FlashArgs {
+    const float *Q;      // [M][n_heads*hd]
+    const void *Kc, *Vc; // as AttnArgs
+    int n_heads, n_kv, hd, s_max;
+    float scale;
+    void *O;             // [M][n_heads*hd] out (dtype, FM)
+    int n_seg;
+    int32_t seg_b[kMaxBatch], seg_pos[kMaxBatch], seg_row[kMaxBatch], seg_len[kMaxBatch];
+};
+void launch_flash_prefill(DType t, const FlashArgs &a, hipStream_t s, const LaunchEvents &ev = {});
 
 struct AttnArgs {
     const float *Q;      // [M][n_heads*hd]
@@ -166,9 +186,6 @@ struct AttnArgs {
     int32_t *counters;   // [max_batch][n_kv][kCounterStride], element 0 of each used; zero between
                          // launches (the merging workgroup resets)
     void *O;             // [M][n_heads*hd] out (dtype, FM)
-    // prefill blocks: causal attention with an online softmax over each row's chunks in one kernel
-    // (no partials; part_o, part_ml, counters unused)
-    int flash;
 };
 // Merge counters sit 256 bytes apart: every chunk workgroup of a (sequence, kv head) takes its
 // counter once, and counters sharing a line would serialise all heads' updates in one place.
@@ -223,8 +240,6 @@ struct UpdateArgs {
     float *u;               // [n][r]
     void *xfm;              // FM scratch for 256 replay rows
     float *Z;               // [n][V] drafter logits -> overwritten by g = dL/dz
-    float *part_val;        // scratch for the logits GEMM epilogue
-    int32_t *part_idx;
     float *row_stats;       // [n][8]
     float *dA;              // [V][r]
     float *du;              // [n][r]

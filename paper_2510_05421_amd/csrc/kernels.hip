@@ -315,309 +315,6 @@ __global__ void __launch_bounds__(256) gemm_fold_kernel(GemmArgs a, int mg) {
     gemm_epilogue<T, 1, EPI>(a, nt, mine, sinv + 16 * g, pre, 16 * g);
 }
 
-// ------------------------------------------------------------------------------------------
-// Large-M GEMM (the prefill: M = batch x prompt block, up to a few thousand tokens; the drafter
-// update's replay rows).  1/rms of each token comes from rms_rows_kernel; the epilogue is the
-// decode GEMM's, per tile, at the wave's token offset.
-// ------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) rms_rows_kernel(const float *ss, int ld_ss, int nparts, int K, float eps,
-                                                       int M, float *out) {
-    const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (m >= M) return;  // uniform across the wave
-    const float v = inv_rms(ss + (size_t)m * ld_ss, nparts, K, eps);
-    if ((threadIdx.x & 63) == 0) out[m] = v;
-}
-
-// ------------------------------------------------------------------------------------------
-// Large-M GEMM staged through LDS (prefill blocks, the drafter update's replay rows).  Workgroup
-// tile of prefill blocks: 128 tokens x 256 features, eight waves as 2 x 4, wave (wy, wx) owning
-// tokens 64 wy .. +63 (four 16-token groups) and features 64 wx .. +63 (four tiles): 16 MFMA tiles,
-// two waves per SIMD, so one wave's LDS reads run under the other's MFMAs (8 x 2048-token prefill
-// 0.33 -> 0.28 s against four waves of 32 tiles).  Per K chunk the workgroup needs 8 activation and
-// 16 weight fragments (1 KiB each, fragment-major in memory and kept so in LDS); at up to 256 rows
-// the tile is 256 tokens x 128 features (waves 4 x 2, 16 activation and 8 weight fragments).  They travel from memory
-// straight into an LDS ring of NS stages with direct-to-LDS loads (each wave loads 3 fragments of
-// every stage), so NS - 1 chunks are in flight while one is multiplied; each wave reads its 4 + 4
-// fragments of the chunk from LDS.  Three stages (72 KiB) let two workgroups share a compute unit
-// (prefill 0.28 -> 0.26 s against four stages).  The waits are explicit: the wave's own ring loads
-// by count (vmcnt), then a workgroup barrier, and the LDS reads are issued as instructions whose
-// completion the wave awaits itself (the compiler would otherwise wait for every ring load before
-// any LDS read).  Every output accumulates its K chunks in increasing order, one MFMA per chunk,
-// whatever the tile it sits in, so a token's result does not depend on M.  Rows or tiles past M or
-// N load clamped (valid) fragments whose products are never stored.  Workgroups are numbered so
-// that each XCD (workgroup id mod 8) takes a contiguous range of tiles, feature block major and
-// token tile minor: consecutive workgroups of one XCD share a weight block through its L2.
-// ------------------------------------------------------------------------------------------
-constexpr int kLdsStages = 3;
-constexpr int kLdsWaves = 8;
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-    // gfx9 s_waitcnt immediate: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8 (others at max)
-    static_assert(N >= 0 && N < 64, "vmcnt range");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xf << 8));
-}
-
-typedef __attribute__((address_space(3))) uint8_t lds_u8;
-
-typedef unsigned v4u32 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint4 as_uint4(v4u32 v) { return uint4{v.x, v.y, v.z, v.w}; }
-
-// The wave's fragments of one chunk, read from LDS and awaited: NX activation groups at xa and NW
-// weight tiles at wa (byte addresses; fragment i is i KiB further).  The reads and the wait are
-// one asm statement, so nothing can use (or copy) a register before its read has completed; the
-// outputs are early-clobber so none of them overwrites an address a later read still needs.
-#define DVI_RD(o, a, off) "ds_read_b128 %" #o ", %" #a " offset:" #off "\n\t"
-template <int NX, int NW>
-__device__ __forceinline__ void lds_fragments(uint32_t xa, uint32_t wa, uint4 (&xf)[NX], uint4 (&wf)[NW]) {
-    v4u32 r[NX + NW];
-    if constexpr (NX == 4 && NW == 4) {
-        asm volatile(DVI_RD(0, 8, 0) DVI_RD(1, 8, 1024) DVI_RD(2, 8, 2048) DVI_RD(3, 8, 3072)
-                     DVI_RD(4, 9, 0) DVI_RD(5, 9, 1024) DVI_RD(6, 9, 2048) DVI_RD(7, 9, 3072) "s_waitcnt lgkmcnt(0)"
-                     : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]),
-                       "=&v"(r[7])
-                     : "v"(xa), "v"(wa));
-    } else if constexpr (NX == 4 && NW == 8) {
-        asm volatile(DVI_RD(0, 12, 0) DVI_RD(1, 12, 1024) DVI_RD(2, 12, 2048) DVI_RD(3, 12, 3072)
-                     DVI_RD(4, 13, 0) DVI_RD(5, 13, 1024) DVI_RD(6, 13, 2048) DVI_RD(7, 13, 3072)
-                     DVI_RD(8, 13, 4096) DVI_RD(9, 13, 5120) DVI_RD(10, 13, 6144) DVI_RD(11, 13, 7168)
-                     "s_waitcnt lgkmcnt(0)"
-                     : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]),
-                       "=&v"(r[7]), "=&v"(r[8]), "=&v"(r[9]), "=&v"(r[10]), "=&v"(r[11])
-                     : "v"(xa), "v"(wa));
-    } else {
-        static_assert(NX == 2 && NW == 4, "fragment counts");
-        asm volatile(DVI_RD(0, 6, 0) DVI_RD(1, 6, 1024) DVI_RD(2, 7, 0) DVI_RD(3, 7, 1024) DVI_RD(4, 7, 2048)
-                     DVI_RD(5, 7, 3072) "s_waitcnt lgkmcnt(0)"
-                     : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5])
-                     : "v"(xa), "v"(wa));
-    }
-#pragma unroll
-    for (int q = 0; q < NX; ++q) xf[q] = as_uint4(r[q]);
-#pragma unroll
-    for (int t = 0; t < NW; ++t) wf[t] = as_uint4(r[NX + t]);
-}
-#undef DVI_RD
-
-// Logits epilogue of the large-M GEMM (the drafter update's 65-256 replay rows): for every
-// output z = sc * acc + gamma * sum_c A_s[n][c] u[m][c], the LoRA sum taken over the rank in
-// increasing order from zero, as the decode GEMM's epilogue takes it.  The workgroup's rows of u
-// and of A_s go into LDS (the ring is free once the K loop is done), 32 rank columns at a time,
-// so each lane reads its factors from LDS instead of gathering them from memory, and the lane's
-// four consecutive logits of a row group leave in one 16-byte store.  Writes logits only: no
-// argmax partials, no sampling (the update asks for neither).
-template <int WV, int XF, int WF, int NW, int GPW>
-__device__ __forceinline__ void lds_logits_epilogue(const GemmArgs &a, const f32x4 (&acc)[NW][GPW], float *smem,
-                                                    int g0, int t0, int wy, int wx) {
-    constexpr int RS = 32, LD = RS + 1;  // rank columns per pass; padded row stride in floats
-    const int lane = threadIdx.x & 63, G4 = lane >> 4;
-    const int NT = a.N / 16;
-    const int m_base = 16 * g0, n_base = 16 * t0;
-    float *us = smem;                // [16 XF rows][LD]
-    float *as = smem + 16 * XF * LD;  // [16 WF rows][LD]
-    float sacc[NW][GPW][4];
-#pragma unroll
-    for (int t = 0; t < NW; ++t)
-#pragma unroll
-        for (int g = 0; g < GPW; ++g)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) sacc[t][g][j] = 0.f;
-    const int r = a.lora_A != nullptr ? a.r : 0;
-    for (int c0 = 0; c0 < r; c0 += RS) {
-        const int rc = min(RS, r - c0);
-        __syncthreads();  // every wave is done with the LDS it read before (ring or last pass)
-        for (int i = threadIdx.x; i < 16 * XF * rc; i += 64 * WV) {
-            const int row = i / rc, c = i - row * rc;
-            us[row * LD + c] = a.lora_u[(size_t)min(m_base + row, a.M - 1) * a.r + c0 + c];
-        }
-        for (int i = threadIdx.x; i < 16 * WF * rc; i += 64 * WV) {
-            const int row = i / rc, c = i - row * rc;
-            as[row * LD + c] = a.lora_A[(size_t)min(n_base + row, NT * 16 - 1) * a.r + c0 + c];
-        }
-        __syncthreads();
-        for (int c = 0; c < rc; ++c) {
-            float uv[GPW];
-#pragma unroll
-            for (int g = 0; g < GPW; ++g) uv[g] = us[(16 * (GPW * wy + g) + (lane & 15)) * LD + c];
-#pragma unroll
-            for (int t = 0; t < NW; ++t)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float av = as[(16 * (NW * wx + t) + 4 * G4 + j) * LD + c];
-#pragma unroll
-                    for (int g = 0; g < GPW; ++g) sacc[t][g][j] += av * uv[g];
-                }
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < NW; ++t) {
-        const int nt = t0 + NW * wx + t;
-#pragma unroll
-        for (int g = 0; g < GPW; ++g) {
-            const int m = m_base + 16 * (GPW * wy + g) + (lane & 15);
-            if (nt < NT && m < a.M) {
-                const float sc = a.ss_in != nullptr ? a.sinv_rows[m] : 1.0f;
-                float y[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    y[j] = acc[t][g][j] * sc;
-                    if (r > 0) y[j] = y[j] + a.gamma * sacc[t][g][j];
-                }
-                *(float4 *)(a.Z + (size_t)m * a.N + nt * 16 + 4 * G4) = make_float4(y[0], y[1], y[2], y[3]);
-            }
-        }
-    }
-}
-
-// WV waves as WY (tokens) x WX (features), every wave tile 16 GPW tokens x 16 NW features.  A
-// chunk has FR = 24 fragments: XF = GPW WY activation groups and WF = FR - XF weight tiles.  A ring
-// stage holds CPS consecutive chunks (KT a multiple of CPS), so the workgroup meets at one barrier
-// per CPS chunks; each wave copies PS = CPS FR / WV of a stage's fragments.
-template <DType T, int EPI, int WV, int WY, int CPS, int GPW>
-__global__ void __launch_bounds__(64 * WV, (WV == 8 && CPS == 1 && EPI == EPI_QKV) ? 4 : 1) gemm_lds_kernel(GemmArgs a, int n_tok_tiles, int n_tiles_total) {
-    constexpr int NS = kLdsStages, FR = 24, PS = CPS * FR / WV;  // stages, fragments per chunk, per wave and stage
-    constexpr int XF = GPW * WY, WF = FR - XF;                     // activation groups, weight tiles per chunk
-    constexpr int WX = WV / WY, NW = WF / WX;                      // waves across the features; tiles per wave
-    static_assert(WX * WY == WV && NW * WX == WF && PS * WV == CPS * FR, "workgroup shape");
-    constexpr uint32_t kChunk = FR * 1024, kStage = CPS * kChunk;
-    __shared__ __align__(1024) uint4 ring[NS][CPS * FR][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wy = wave / WX, wx = wave - wy * WX;
-    const int KC = (T == DType::BF16) ? 32 : 16;
-    const int KT = a.K / KC, NT = a.N / 16, NG = (a.M + 15) / 16;
-    // workgroup -> (token tile, feature block): XCD x = id % 8 takes tiles [x * per, (x+1) * per)
-    const int per = (n_tiles_total + 7) / 8;
-    const int j = blockIdx.x >> 3;
-    const int tl = (blockIdx.x & 7) * per + j;
-    if (j >= per || tl >= n_tiles_total) return;  // uniform across the workgroup (before any barrier)
-    const int g0 = (tl % n_tok_tiles) * XF, t0 = (tl / n_tok_tiles) * WF;
-    // the stage fragments this wave copies: f = PS * wave + i is fragment fr = f % FR of the
-    // stage's chunk f / FR; fr < XF: activation group g0 + fr, else weight tile t0 + fr - XF
-    // (clamped into range).  Stage layout: fragment f at f KiB.
-    const uint4 *src[PS];
-    int coff[PS];
-#pragma unroll
-    for (int i = 0; i < PS; ++i) {
-        const int f = PS * wave + i, fr = CPS == 1 ? f : f % FR;  // with one chunk, f < FR already
-        coff[i] = CPS == 1 ? 0 : f / FR;
-        src[i] = (fr < XF ? (const uint4 *)a.X + (size_t)min(g0 + fr, NG - 1) * KT * 64
-                          : (const uint4 *)a.W + (size_t)min(t0 + fr - XF, NT - 1) * KT * 64) + lane;
-    }
-    lds_u8 *const ring0 = (lds_u8 *)&ring[0][0][0];
-    // stage st <- chunks CPS k .. CPS k + CPS - 1
-    auto issue = [&](int st, int k) {
-#pragma unroll
-        for (int i = 0; i < PS; ++i)
-            __builtin_amdgcn_global_load_lds((const void *)(src[i] + (size_t)(CPS * k + coff[i]) * 64),
-                                             (__attribute__((address_space(3))) void *)(ring0 + st * kStage +
-                                                                                         (PS * wave + i) * 1024),
-                                             16, 0, 0);
-    };
-    // this lane's LDS byte address in fragment 0 of stage 0; fragment f of stage st is f KiB and
-    // st stages further
-    const uint32_t lbase = (uint32_t)(uintptr_t)ring0 + 16 * lane;
-    f32x4 acc[NW][GPW];
-#pragma unroll
-    for (int t = 0; t < NW; ++t)
-#pragma unroll
-        for (int g = 0; g < GPW; ++g) acc[t][g] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const int KS = KT / CPS;  // stages of the K loop
-#pragma unroll
-    for (int st = 0; st < NS - 1; ++st)
-        if (st < KS) issue(st, st);
-    for (int k = 0; k < KS; ++k) {
-        // stage k's loads are done once at most min(NS - 2, KS - 1 - k) later stages are in flight
-        const int later = min(NS - 2, KS - 1 - k);
-        static_assert(NS - 2 <= 4, "wait cases");
-        if (later >= 4) wait_vmcnt<4 * PS>();
-        else if (later == 3) wait_vmcnt<3 * PS>();
-        else if (later == 2) wait_vmcnt<2 * PS>();
-        else if (later == 1) wait_vmcnt<PS>();
-        else wait_vmcnt<0>();
-        // every wave's fragments of stage k are in LDS, and every wave is done with the stage the
-        // next issue overwrites (its LDS reads of stage k - 1 completed before its MFMAs)
-        __builtin_amdgcn_s_barrier();
-        if (k + NS - 1 < KS) issue((k + NS - 1) % NS, k + NS - 1);
-#pragma unroll
-        for (int cc = 0; cc < CPS; ++cc) {
-            const uint32_t sb = lbase + (uint32_t)(k % NS) * kStage + cc * kChunk;
-            uint4 xf[GPW], wf[NW];
-            lds_fragments<GPW, NW>(sb + GPW * wy * 1024, sb + (XF + NW * wx) * 1024, xf, wf);
-#pragma unroll
-            for (int t = 0; t < NW; ++t)
-#pragma unroll
-                for (int g = 0; g < GPW; ++g) acc[t][g] = St<T>::mma(wf[t], xf[g], acc[t][g]);
-        }
-    }
-    if constexpr (EPI == EPI_LOGITS) {
-        lds_logits_epilogue<WV, XF, WF, NW, GPW>(a, acc, (float *)&ring[0][0][0], g0, t0, wy, wx);
-        return;
-    } else {
-        const int gw = g0 + GPW * wy;
-        if (gw >= NG) return;  // uniform across the wave
-        const int m0 = 16 * gw;
-#pragma unroll
-        for (int t = 0; t < NW; ++t) {
-            const int nt = t0 + NW * wx + t;
-            if (nt < NT) {  // uniform; a guard, not a break, so the loop unrolls and acc stays in registers
-                EpiOperands<GPW> pre;
-                epilogue_prefetch<GPW, EPI>(a, nt, pre, m0);
-                epilogue_prefetch_rope<GPW, EPI>(a, nt, pre);
-                gemm_epilogue<T, GPW, EPI>(a, nt, acc[t], a.sinv_rows + m0, pre, m0);
-            }
-        }
-    }
-}
-
-template <DType T, int EPI, int WV, int WY, int CPS, int GPW>
-static void launch_gemm_lds_shape(const GemmArgs &a, hipStream_t s, const LaunchEvents &ev) {
-    constexpr int XF = GPW * WY, WF = 24 - XF;
-    const int tok = (a.M + 16 * XF - 1) / (16 * XF), blk = (a.N / 16 + WF - 1) / WF, total = tok * blk;
-    const int grid = 8 * ((total + 7) / 8);
-    if (ev.start || ev.stop)
-        hipExtLaunchKernelGGL(gemm_lds_kernel<T, EPI, WV, WY, CPS, GPW>, dim3(grid), dim3(64 * WV), 0, s, ev.start, ev.stop, 0, a,
-                              tok, total);
-    else
-        gemm_lds_kernel<T, EPI, WV, WY, CPS, GPW><<<grid, 64 * WV, 0, s>>>(a, tok, total);
-}
-
-template <DType T, int EPI>
-static void launch_gemm_lds(const GemmArgs &a, hipStream_t s, const LaunchEvents &ev) {
-    // up to 256 rows (the drafter update): one token tile of 256 rows, so each weight block is read
-    // by one workgroup (update forward 94 -> 91 us at the 7B head, full-ring update 0.450 ->
-    // 0.409 ms), and, the grid being one workgroup per compute unit, ring stages of two chunks
-    // (144 KiB, one barrier per two chunks: 91 -> 89 us).  The update's logits take 16 waves of
-    // 32 x 64 tiles (four waves per SIMD in 116 registers instead of two: 89 -> 85 us).  Prefill
-    // blocks: 128 rows x 256 features, one-chunk stages (72 KiB); QKV under a 128-register bound
-    // (its epilogue spills 28 bytes) so that two workgroups share a compute unit, as gate/up's
-    // 112 registers allow anyway (8 x 2048 prefill QKV 261 -> 232 us).  Out-proj/down (136
-    // registers, one workgroup per compute unit) take the update's arrangement instead: 16 waves
-    // of 32 x 64 tiles over two-chunk stages, four waves per SIMD (149 -> 137-141 us); gate/up and
-    // QKV lose with it (347 -> 395, 232 -> 245 us).
-    const int KT = a.K / ((T == DType::BF16) ? 32 : 16);
-    if constexpr (EPI == EPI_LOGITS) {
-        if (KT % 2 == 0) launch_gemm_lds_shape<T, EPI, 16, 8, 2, 2>(a, s, ev);
-        else launch_gemm_lds_shape<T, EPI, kLdsWaves, 4, 1, 4>(a, s, ev);
-    } else {
-        if (a.M <= 256 && KT % 2 == 0) launch_gemm_lds_shape<T, EPI, kLdsWaves, 4, 2, 4>(a, s, ev);
-        else if (a.M <= 256) launch_gemm_lds_shape<T, EPI, kLdsWaves, 4, 1, 4>(a, s, ev);
-        else if (EPI == EPI_RESID && KT % 2 == 0) launch_gemm_lds_shape<T, EPI, 16, 4, 2, 2>(a, s, ev);
-        else launch_gemm_lds_shape<T, EPI, kLdsWaves, 2, 1, 4>(a, s, ev);
-    }
-}
-
-template <DType T>
-static void launch_gemm_big(Epi e, const GemmArgs &a, hipStream_t s, const LaunchEvents &ev) {
-    if (a.ss_in != nullptr)
-        rms_rows_kernel<<<(a.M + 3) / 4, 256, 0, s>>>(a.ss_in, a.ld_ss_in, a.K / 16, a.K, a.eps, a.M, a.sinv_rows);
-    switch (e) {
-        case EPI_RESID: launch_gemm_lds<T, EPI_RESID>(a, s, ev); break;
-        case EPI_QKV: launch_gemm_lds<T, EPI_QKV>(a, s, ev); break;
-        case EPI_SWIGLU: launch_gemm_lds<T, EPI_SWIGLU>(a, s, ev); break;
-        default: break;  // the heads run on at most 64 rows (launch_gemm rejects more)
-    }
-}
-
 // Launch shape of a weight matrix, a function of (N, K) only, never of M: RT 16-row tiles
 // per workgroup (activations reused across them) and the K split over the workgroup's waves.
 // Since neither depends on M, every output's summation order is the same for every call on
@@ -760,14 +457,7 @@ static void launch_split_epi(Epi e, const GemmArgs &a, const GemmShape &sh, hipS
 }
 
 bool launch_gemm(DType t, Epi e, const GemmArgs &a, hipStream_t s, const LaunchEvents &ev) {
-    if (a.M > 64 || a.large_m) {
-        if (e == EPI_LOGITS) return false;
-        if (t == DType::BF16)
-            launch_gemm_big<DType::BF16>(e, a, s, ev);
-        else
-            launch_gemm_big<DType::F32>(e, a, s, ev);
-        return true;
-    }
+    if (a.M > 64) return false;
     const GemmShape sh = gemm_shape(a.N, a.K, pack_kc(t), a.M);
     if (a.kpart != nullptr && a.M > 32 && split_fits(sh, a.K, pack_kc(t), (a.M + 15) / 16)) {
         if (t == DType::BF16)
@@ -910,29 +600,6 @@ void launch_gather_fm(DType t, const void *src, bool src_fm, int rs, int off, in
         gather_fm_kernel<DType::BF16><<<rows, 256, 0, s>>>(src, src_fm ? 1 : 0, rs, off, K, dst);
     else
         gather_fm_kernel<DType::F32><<<rows, 256, 0, s>>>(src, src_fm ? 1 : 0, rs, off, K, dst);
-}
-
-// The prefill's head input when prompts differ in length: each sequence's last prompt row of a
-// block (its folded-norm input dtype(h * g_final) and the row's partial sums of squares) goes to
-// row b of compact buffers.  Workgroup b.
-template <DType T>
-__global__ void __launch_bounds__(256) gather_last_kernel(const void *hg, const float *ss, int block_len, int d,
-                                                          int nps, LastRows lr, void *dst, float *ss_dst) {
-    const int b = blockIdx.x;
-    const int i = lr.src[b];
-    if (i < 0) return;  // uniform across the workgroup
-    const int r = b * block_len + i;
-    for (int k = threadIdx.x; k < d; k += 256) St<T>::store(dst, fm_index<T>(b, k, d), St<T>::load(hg, fm_index<T>(r, k, d)));
-    for (int k = threadIdx.x; k < nps; k += 256) ss_dst[(size_t)b * nps + k] = ss[(size_t)r * nps + k];
-}
-
-void launch_gather_last(DType t, const void *hg, const float *ss, int block_len, int d, int nps, int B,
-                        const LastRows &lr, void *dst, float *ss_dst, hipStream_t s) {
-    if (B <= 0) return;
-    if (t == DType::BF16)
-        gather_last_kernel<DType::BF16><<<B, 256, 0, s>>>(hg, ss, block_len, d, nps, lr, dst, ss_dst);
-    else
-        gather_last_kernel<DType::F32><<<B, 256, 0, s>>>(hg, ss, block_len, d, nps, lr, dst, ss_dst);
 }
 
 // u[m][c] = sum_i B_s[c][i] x[m][i] for already-normalised rows x.  Workgroup (c, m).
@@ -1372,118 +1039,6 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(AttnArgs a) {
     merge_row<T, HD>(a, m, h, (a.lens[b] + a.pos_off + i) / CK + 1, lane);
 }
 
-// Causal attention of a prefill block, flash-style: each query row's softmax runs online over its
-// 64-key chunks in increasing order, and no partials leave the workgroup.  Workgroup (tile x, kv
-// head, sequence b) of four waves; wave w owns rows r0 = 64 x + 16 w .. +15 of the R = c * G rows
-// that read this kv head (row r = i * G + gi: position len0 + i, head kvh * G + gi), as the MFMA
-// row dimension.  Per chunk: S = Q K^T, the chunk's row maxima, a rescale of the running sum and
-// output by exp(m_old - m_new), P = exp(S - m_new) through the wave's LDS tile into A-operand
-// layout, O += P V.  A row's arithmetic depends only on its position and the cache: chunks past a
-// row's position have every key masked and leave its max, sum and output exactly as they were, so
-// results do not depend on how the prompt is cut into blocks or on the rows sharing a tile.
-template <DType T, int HD>
-__global__ void __launch_bounds__(256) flash_prefill_kernel(AttnArgs a) {
-    typedef AttnTile<T, HD> A;
-    typedef typename St<T>::type E;
-    __shared__ __align__(16) E Ps[4][16][A::PST];
-    const int kvh = blockIdx.y, b = blockIdx.z;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, l16 = lane & 15, lg = lane >> 4;
-    const int G = a.n_heads / a.n_kv, R = a.c * G;
-    const int r0 = 64 * blockIdx.x + 16 * w;
-    if (r0 >= R) return;  // uniform across the wave; no workgroup barrier follows
-    const int len0 = a.lens[b] + a.pos_off;
-    const int last_ch = (len0 + min(r0 + 15, R - 1) / G) / CK;  // chunk of the tile's last position
-    const int nwritten = len0 + a.c;                             // cache positions holding keys/values
-    uint4 qf[A::DS];
-    {
-        typename A::QRaw qraw;
-        A::load_q(a, b, kvh, r0, qraw);
-        A::pack_q(qraw, r0, R, qf);
-    }
-    float m_run[4], l_run[4];
-    int rpos[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int r = r0 + 4 * lg + j;
-        m_run[j] = -INFINITY;
-        l_run[j] = 0.f;
-        rpos[j] = r < R ? len0 + r / G : -1;
-    }
-    f32x4 O[A::DT];
-#pragma unroll
-    for (int dt = 0; dt < A::DT; ++dt) O[dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    for (int ch = 0; ch <= last_ch; ++ch) {
-        const int kbase = ch * CK;
-        f32x4 S[4];
-        {
-            typename A::KFrag kf;
-            A::load_k(a, b, kvh, ch, kf);
-            __builtin_amdgcn_sched_barrier(0);
-            A::scores(qf, kf, S);
-        }
-        typename A::VFrag vf;
-        A::load_v(a, b, kvh, ch, vf);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int nvalid = rpos[j] >= 0 ? min(CK, rpos[j] + 1 - kbase) : 0;
-            float mx = -INFINITY;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float sv = (16 * t + l16 < nvalid) ? S[t][j] * a.scale : -INFINITY;
-                S[t][j] = sv;
-                mx = fmaxf(mx, sv);
-            }
-            mx = row16_max(mx);
-            const float mnew = fmaxf(m_run[j], mx);
-            const float alpha = mnew == -INFINITY ? 1.f : exp_fast(m_run[j] - mnew);
-            float ps = 0.f;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float pv = mnew == -INFINITY ? 0.f : exp_fast(S[t][j] - mnew);
-                S[t][j] = pv;
-                ps += pv;
-            }
-            ps = row16_sum(ps);
-            l_run[j] = l_run[j] * alpha + ps;
-            m_run[j] = mnew;
-#pragma unroll
-            for (int dt = 0; dt < A::DT; ++dt) O[dt][j] *= alpha;
-        }
-        // P -> LDS (row-major, dtype), then back as A fragments
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) St<T>::store(&Ps[w][4 * lg + j][0], 16 * t + l16, S[t][j]);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        uint4 pf[A::KS];
-#pragma unroll
-        for (int ks = 0; ks < A::KS; ++ks) pf[ks] = *(const uint4 *)&Ps[w][l16][ks * A::KC + A::EPL * lg];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // keys past the written positions may hold anything: their values enter as zeros
-        const int nk = min(CK, nwritten - kbase);
-#pragma unroll
-        for (int dt = 0; dt < A::DT; ++dt)
-#pragma unroll
-            for (int ks = 0; ks < A::KS; ++ks)
-                O[dt] = St<T>::mma(pf[ks], mask_keys<T>(vf[dt][ks], ks * A::KC + A::EPL * lg, nk), O[dt]);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int r = r0 + 4 * lg + j;
-        if (r >= R) continue;
-        const int i = r / G, gi = r - i * G;
-        const int m = b * a.c + i, h = kvh * G + gi;
-#pragma unroll
-        for (int dt = 0; dt < A::DT; ++dt)
-            St<T>::store(a.O, fm_index<T>(m, h * HD + 16 * dt + l16, a.n_heads * HD), O[dt][j] / l_run[j]);
-    }
-}
-
 template <DType T, int HD>
 static void launch_attention_t(const AttnArgs &a, hipStream_t s, const LaunchEvents &ev) {
     // One wave per 64-key chunk, four chunks per workgroup: the workgroup that finishes last
@@ -1497,10 +1052,6 @@ static void launch_attention_t(const AttnArgs &a, hipStream_t s, const LaunchEve
     // and the last merges would run at the kernel's tail, each wave merging several rows one
     // after another (6 rows: 17.1 -> 16.0 us, 20 rows: 18.6 -> 15.7 us with the second launch).
     const int rows = a.c * (a.n_heads / a.n_kv);
-    if (a.flash) {
-        launch_timed(flash_prefill_kernel<T, HD>, dim3((rows + 63) / 64, a.n_kv, a.B), dim3(256), s, ev, a);
-        return;
-    }
     const long waves = (long)a.n_chunks * a.n_kv * a.B;
     if (waves >= kAttnLargeGrid || rows > 4) {
         const int all_rows = a.B * a.c * a.n_heads;
@@ -2075,42 +1626,18 @@ void launch_update_forward(DType t, const UpdateArgs &u, hipStream_t s) {
         launch_gather_fm(t, u.Hh, false, 1, r0, rows, u.d, u.xfm, s);
         const float *ur = u.u + (size_t)r0 * u.rank;
         float *Zr = u.Z + (size_t)r0 * u.V;
-        if (rows <= 64) {
-            // up to four row groups: the decode GEMM (K split over the waves) with its LoRA
-            // epilogue streams the head fastest
-            GemmArgs g{};
-            g.W = u.W;
-            g.X = u.xfm;
-            g.M = rows;
-            g.N = u.V;
-            g.K = u.d;
-            g.Z = Zr;
-            g.part_val = u.part_val;
-            g.part_idx = u.part_idx;
-            g.lora_A = u.A;
-            g.lora_u = ur;
-            g.r = u.rank;
-            g.gamma = u.gamma;
-            launch_gemm(t, EPI_LOGITS, g, s);
-        } else {
-            // 65 to 256 rows: the LDS-staged large-M GEMM (each workgroup 128 rows x 256
-            // vocabulary entries), its logits epilogue with the LoRA term and no argmax partials
-            GemmArgs g{};
-            g.W = u.W;
-            g.X = u.xfm;
-            g.M = rows;
-            g.N = u.V;
-            g.K = u.d;
-            g.Z = Zr;
-            g.lora_A = u.A;
-            g.lora_u = ur;
-            g.r = u.rank;
-            g.gamma = u.gamma;
-            if (t == DType::BF16)
-                launch_gemm_lds<DType::BF16, EPI_LOGITS>(g, s, LaunchEvents{});
-            else
-                launch_gemm_lds<DType::F32, EPI_LOGITS>(g, s, LaunchEvents{});
-        }
+        GemmArgs g{};
+        g.W = u.W;
+        g.X = u.xfm;
+        g.M = rows;
+        g.N = u.V;
+        g.K = u.d;
+        g.Z = Zr;
+        g.lora_A = u.A;
+        g.lora_u = ur;
+        g.r = u.rank;
+        g.gamma = u.gamma;
+        launch_gemm_rows(t, EPI_LOGITS, g, s);
     }
     if (u.V <= 4096)
         upd_rows_kernel<4><<<u.n, 1024, 0, s>>>(u, counts);
