@@ -245,7 +245,7 @@ static size_t layout(dvi_ctx *x, const dvi_config &c, void *base) {
     void *hk_hat = b.take<void>(Bk * d * es);
     void *dfm = b.take<void>(B16 * d * es);
     void *pfm = b.take<void>(B16 * d * es);
-    void *ufm = b.take<void>((size_t)256 * d * es);
+    void *ufm = b.take<void>((R + 15) / 16 * 16 * d * es);
     float *vlogits = b.take<float>(M * V * 4);
     float *dlogits = b.take<float>((size_t)c.max_batch * V * 4);
     float *part_val = b.take<float>(M * (V / 16) * 4);
@@ -1228,11 +1228,6 @@ extern "C" dvi_status dvi_abort_step(dvi_ctx *x) {
 // ------------------------------------------------------------------------------------------
 // C ABI: drafter update
 // ------------------------------------------------------------------------------------------
-__global__ void clear_i8_kernel(int8_t *p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
-
 extern "C" dvi_status dvi_update_drafter(dvi_ctx *x, const dvi_update_args *ua, dvi_update_stats *stats) {
     if (!x || !ua) return DVI_ERR_ARG;
     if (x->device_error) return fail(x, DVI_ERR_DEVICE, "context has a sticky device error");
@@ -1276,17 +1271,26 @@ extern "C" dvi_status dvi_update_drafter(dvi_ctx *x, const dvi_update_args *ua, 
     launch_update_forward(x->dt, u, x->stream);
     launch_update_backward(x->dt, u, x->stream);
     const size_t nA = (size_t)cf.vocab * cf.lora_rank, nB = (size_t)cf.lora_rank * cf.d_model;
-    if (ua->grad_A_out)
-        HIPCHK(x, hipMemcpyAsync(ua->grad_A_out, x->upd_dA, nA * 4, hipMemcpyDeviceToDevice, x->stream));
-    if (ua->grad_B_out)
-        HIPCHK(x, hipMemcpyAsync(ua->grad_B_out, x->upd_dB, nB * 4, hipMemcpyDeviceToDevice, x->stream));
-    if (ua->lr != 0.f) {
-        launch_adam(x->lora_A, x->upd_dA, x->mA, x->vA, (int)nA, ua->lr, ua->beta1, ua->beta2, ua->eps, ua->opt_step,
-                    x->stream);
-        launch_adam(x->lora_B, x->upd_dB, x->mB, x->vB, (int)nB, ua->lr, ua->beta1, ua->beta2, ua->eps, ua->opt_step,
-                    x->stream);
-    }
-    clear_i8_kernel<<<(cf.buffer_rows + 255) / 256, 256, 0, x->stream>>>(x->ring_fresh, cf.buffer_rows);
+    FinishArgs f{};
+    f.gA = x->upd_dA;
+    f.gB = x->upd_dB;
+    f.outA = ua->grad_A_out;
+    f.outB = ua->grad_B_out;
+    f.A = x->lora_A;
+    f.B = x->lora_B;
+    f.mA = x->mA;
+    f.vA = x->vA;
+    f.mB = x->mB;
+    f.vB = x->vB;
+    f.nA = (long)nA;
+    f.nB = (long)nB;
+    f.fresh = x->ring_fresh;
+    f.ring_rows = cf.buffer_rows;
+    f.lr = ua->lr;
+    f.b1 = ua->beta1;
+    f.b2 = ua->beta2;
+    f.eps = ua->eps;
+    launch_update_finish(f, ua->opt_step, x->stream);
     ev_end(x, 3);
     LAUNCHCHK(x);
     float lo[16];

@@ -134,10 +134,6 @@ void launch_embed(DType t, const void *emb, const int32_t *tok, int tok_stride, 
 void launch_head_prep(DType t, const float *h, int ldh, const float *ss, int ld_ss, const float *g, int M, int d,
                       float eps, const float *Bm, int r, void *xhat, int ldx, void *xfm, float *u, hipStream_t s);
 
-// dst (FM) row i = src row i*rs + off; src is FM when src_fm, else row-major [..][K].
-void launch_gather_fm(DType t, const void *src, bool src_fm, int rs, int off, int rows, int K, void *dst,
-                      hipStream_t s);
-
 constexpr int kMaxBatch = 64;
 
 // The rows of a prefill block, M rows from row t0 of the prompts laid end to end (ids; sequence b's
@@ -192,9 +188,6 @@ struct AttnArgs {
 constexpr int kCounterStride = 64;
 void launch_attention(DType t, const AttnArgs &a, hipStream_t s, const LaunchEvents &ev = {});
 
-// u[m][c] = sum_i B[c][i] * x[m][i]   (x dtype, B fp32 [r][d])
-void launch_lora_u(DType t, const void *x, const float *Bm, int M, int d, int r, float *u, hipStream_t s);
-
 // Per-row argmax over the per-tile partials (ties -> lowest id).  out[m * out_stride] =
 // forced ? forced[m * out_stride] : argmax; flags[0] |= 1 on non-finite logits.
 void launch_argmax(const float *part_val, const int32_t *part_idx, int M, int ntiles, int32_t *out,
@@ -238,7 +231,7 @@ struct UpdateArgs {
     float gamma, tau, baseline, c_kl, c_ce, c_pg, c_ent;
     const float *A, *Bm;    // A_s [V][r], B_s [r][d]
     float *u;               // [n][r]
-    void *xfm;              // FM scratch for 256 replay rows
+    void *xfm;              // FM scratch [n][d]
     float *Z;               // [n][V] drafter logits -> overwritten by g = dL/dz
     float *row_stats;       // [n][8]
     float *dA;              // [V][r]
@@ -249,8 +242,17 @@ struct UpdateArgs {
 };
 void launch_update_forward(DType t, const UpdateArgs &u, hipStream_t s);
 void launch_update_backward(DType t, const UpdateArgs &u, hipStream_t s);
-void launch_adam(float *p, const float *g, float *m, float *v, int n, float lr, float b1, float b2,
-                 float eps, int step, hipStream_t s);
+// The update's end: gradients out (outA, outB: may be null), Adam unless lr == 0, fresh flags cleared.
+struct FinishArgs {
+    const float *gA, *gB;   // gradients [nA], [nB]
+    float *outA, *outB;
+    float *A, *B, *mA, *vA, *mB, *vB;
+    long nA, nB;
+    int8_t *fresh;          // [ring_rows]
+    int ring_rows;
+    float lr, b1, b2, eps, c1, c2;  // c1, c2: bias corrections, from the step number
+};
+void launch_update_finish(FinishArgs f, int step, hipStream_t s);
 
 // Streaming-read reference: every 16-byte word of buf[0, bytes) read once with the decode GEMM's
 // non-temporal loads (bytes a multiple of 16); the XOR of everything read goes to sink[0] only

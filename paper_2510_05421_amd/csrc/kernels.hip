@@ -581,47 +581,6 @@ void launch_head_prep(DType t, const float *h, int ldh, const float *ss, int ld_
         head_prep_kernel<DType::F32><<<grid, 256, 0, s>>>(h, ldh, ss, ld_ss, g, d, eps, Bm, r, xhat, ldx, xfm, u);
 }
 
-// Gather rows into a compact FM buffer: dst row i = src row (i * rs + off) (FM or row-major
-// source), K columns.  Used for the prefill head (last token of every sequence) and for the
-// drafter update (replay rows).
-template <DType T>
-__global__ void __launch_bounds__(256) gather_fm_kernel(const void *src, int src_fm, int rs, int off, int K, void *dst) {
-    const int i = blockIdx.x, r = i * rs + off;
-    for (int k = threadIdx.x; k < K; k += 256) {
-        const float v = St<T>::load(src, src_fm ? fm_index<T>(r, k, K) : (size_t)r * K + k);
-        St<T>::store(dst, fm_index<T>(i, k, K), v);
-    }
-}
-
-void launch_gather_fm(DType t, const void *src, bool src_fm, int rs, int off, int rows, int K, void *dst,
-                      hipStream_t s) {
-    if (rows <= 0) return;
-    if (t == DType::BF16)
-        gather_fm_kernel<DType::BF16><<<rows, 256, 0, s>>>(src, src_fm ? 1 : 0, rs, off, K, dst);
-    else
-        gather_fm_kernel<DType::F32><<<rows, 256, 0, s>>>(src, src_fm ? 1 : 0, rs, off, K, dst);
-}
-
-// u[m][c] = sum_i B_s[c][i] x[m][i] for already-normalised rows x.  Workgroup (c, m).
-template <DType T>
-__global__ void __launch_bounds__(256) lora_u_kernel(const void *x, const float *Bm, int d, int r, float *u) {
-    __shared__ float red[4];
-    const int c = blockIdx.x, m = blockIdx.y;
-    float acc = 0.f;
-    for (int i = threadIdx.x; i < d; i += 256) acc += Bm[(size_t)c * d + i] * St<T>::load(x, (size_t)m * d + i);
-    acc = block_sum256(acc, red);
-    if (threadIdx.x == 0) u[(size_t)m * r + c] = acc;
-}
-
-void launch_lora_u(DType t, const void *x, const float *Bm, int M, int d, int r, float *u, hipStream_t s) {
-    if (M <= 0) return;
-    dim3 grid(r, M);
-    if (t == DType::BF16)
-        lora_u_kernel<DType::BF16><<<grid, 256, 0, s>>>(x, Bm, d, r, u);
-    else
-        lora_u_kernel<DType::F32><<<grid, 256, 0, s>>>(x, Bm, d, r, u);
-}
-
 // ------------------------------------------------------------------------------------------
 // Block-causal attention against the KV cache, on MFMA: split over 64-key chunks at absolute
 // positions (attn_chunk), then a merge of every row's chunks in chunk order (merge_fold).
@@ -1251,29 +1210,56 @@ void launch_ring_copy(const int32_t *cl, int max_rows, const void *hk_hat, int d
 // Drafter update (Section 3.4).  Forward logits use the MFMA GEMM (EPI_LOGITS with LoRA);
 // these kernels turn them into the loss gradient and the LoRA-factor gradients.
 // ------------------------------------------------------------------------------------------
-// stats[0] = n rows, [1] = accepted rows, [2] = fresh rows, [3] = fresh accepted rows.
-// Row counts of the ring (all, accepted, fresh, fresh and accepted): one wave, lane-strided, the
-// integer sums reduced across the wave (exact in any order).
-__global__ void upd_counts_kernel(const int8_t *r, const int8_t *fresh, int n, float *stats) {
-    const int lane = threadIdx.x & 63;
-    int na = 0, nf = 0, nfa = 0;
-    for (int i = lane; i < n; i += 64) {
-        const bool acc = r[i] != 0, fr = fresh[i] != 0;
-        na += acc;
-        nf += fr;
-        nfa += acc && fr;
-    }
+// What the update needs of the replay rows before its GEMM, in one launch (the three parts do not
+// depend on each other and none fills the chip; as launches of their own: counts 2.5, u 15, FM copy 8
+// us at 256 rows of d = 5120): workgroups 0 .. n r - 1 the projections u[m][c] = sum_i B_s[c][i] x[m][i]
+// of row m = id / r, rank c = id % r; the next n the row's copy into the FM layout; the last the row
+// counts (all, accepted, fresh, fresh and accepted; integer sums, exact in any order).  Bound by the
+// L2 reads of x and B_s (each workgroup of the first part streams a row of both), so 16-byte loads.
+template <DType T>
+__global__ void __launch_bounds__(256) upd_prep_kernel(UpdateArgs u, float *counts) {
+    typedef typename St<T>::type E;
+    constexpr int EPL = 16 / (int)sizeof(E);
+    __shared__ float red[4];
+    const int id = blockIdx.x, nq = u.d / EPL;
+    if (id < u.n * u.rank) {
+        const int m = id / u.rank, c = id - m * u.rank;
+        const uint4 *x = (const uint4 *)((const E *)u.Hh + (size_t)m * u.d);
+        const float *bm = u.Bm + (size_t)c * u.d;
+        float acc = 0.f;
+        for (int q = threadIdx.x; q < nq; q += 256) {
+            float xv[EPL];
+            unpack_frag<T>(x[q], xv);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        na += __shfl_xor(na, o);
-        nf += __shfl_xor(nf, o);
-        nfa += __shfl_xor(nfa, o);
-    }
-    if (lane == 0) {
-        stats[0] = (float)n;
-        stats[1] = (float)na;
-        stats[2] = (float)nf;
-        stats[3] = (float)nfa;
+            for (int e = 0; e < EPL; ++e) acc += bm[q * EPL + e] * xv[e];
+        }
+        acc = block_sum256(acc, red);
+        if (threadIdx.x == 0) u.u[id] = acc;
+    } else if (id < u.n * (u.rank + 1)) {
+        const int m = id - u.n * u.rank;
+        const uint4 *x = (const uint4 *)((const E *)u.Hh + (size_t)m * u.d);
+        for (int q = threadIdx.x; q < nq; q += 256) *(uint4 *)((E *)u.xfm + fm_index<T>(m, q * EPL, u.d)) = x[q];
+    } else if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        int na = 0, nf = 0, nfa = 0;
+        for (int i = lane; i < u.n; i += 64) {
+            const bool acc = u.r[i] != 0, fr = u.fresh[i] != 0;
+            na += acc;
+            nf += fr;
+            nfa += acc && fr;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            na += __shfl_xor(na, o);
+            nf += __shfl_xor(nf, o);
+            nfa += __shfl_xor(nfa, o);
+        }
+        if (lane == 0) {
+            counts[0] = (float)u.n;
+            counts[1] = (float)na;
+            counts[2] = (float)nf;
+            counts[3] = (float)nfa;
+        }
     }
 }
 
@@ -1393,9 +1379,9 @@ __global__ void __launch_bounds__(1024) upd_rows_kernel(UpdateArgs u, const floa
     }
 }
 
-// The loss and its terms, summed over the ring rows: one wave, lane l adding rows l, l + 64, ...
+// The loss and its terms, summed over the ring rows by one wave, lane l adding rows l, l + 64, ...
 // in order, then the fixed wave tree.
-__global__ void upd_loss_kernel(UpdateArgs u, const float *counts) {
+__device__ __forceinline__ void upd_loss(const UpdateArgs &u, const float *counts) {
     const int lane = threadIdx.x & 63;
     float loss = 0.f, kl = 0.f, ent = 0.f, ce = 0.f, pg = 0.f;
     for (int i = lane; i < u.n; i += 64) {
@@ -1466,8 +1452,9 @@ __device__ __forceinline__ void stage_rank_slice(float (&dst)[256][16], const fl
 // dA[v][c] = gamma sum_i g[i][v] u[i][c] and du[i][c] = gamma sum_v A_s[v][c] g[i][v], g = dL/dz
 // (the rows of Z after upd_rows_kernel), in one pass over g for the 16 ranks c0 .. c0 + 15.  A
 // workgroup takes kGradV = 128 vocabulary entries, two per lane (v0 = 128 b + 2 l, v0 + 1), and
-// every row: per block of 256 rows, the block's u slice goes to LDS and wave w takes rows 32 w ..
-// 32 w + 31 of the block, eight rows' loads of g in flight.  A lane keeps its two entries' rows
+// every row: per block of up to 256 rows, the block's u slice goes to LDS and the eight waves take an
+// eighth of its rows each (48 rows in blocks of 32 per wave left six waves idle: 20 us), eight rows'
+// loads of g in flight.  A lane keeps its two entries' rows
 // of A_s and their 16 dA sums (its rows in order; the eight waves are then added in order through
 // LDS).  Per row it forms the two entries' share of du for the 16 ranks, which transpose_sum16
 // reduces over the wave, and the workgroup's share goes to du_part[b][i][16]; upd_du_sum_kernel
@@ -1496,7 +1483,8 @@ __global__ void __launch_bounds__(64 * kGradWaves) upd_grad_kernel(UpdateArgs u,
         __syncthreads();  // every wave is done with the previous block's slice
         stage_rank_slice(us, u.u, u.n, u.rank, rb, c0, 64 * kGradWaves);
         __syncthreads();
-        const int i0 = min(u.n, rb + 32 * w), i1 = min(u.n, i0 + 32);
+        const int rpw = (min(256, u.n - rb) + kGradWaves - 1) / kGradWaves;  // rows per wave
+        const int i0 = min(u.n, rb + rpw * w), i1 = min(u.n, i0 + rpw);
         for (int ib = i0; ib < i1; ib += 8) {
             float2 g2[8];
 #pragma unroll
@@ -1547,9 +1535,14 @@ __global__ void __launch_bounds__(64 * kGradWaves) upd_grad_kernel(UpdateArgs u,
 
 // du[i][c0 + c] = gamma * (sum of the nb workgroups' shares du_part[b][i][c]).  One workgroup
 // per row; thread (j, c) adds the shares of workgroups [j P, (j + 1) P) in order (P = ceil(nb /
-// 16)), then the sixteen partial sums are added in order.
-__global__ void __launch_bounds__(256) upd_du_sum_kernel(UpdateArgs u, int c0, int nb) {
+// 16)), then the sixteen partial sums are added in order.  Workgroup n, in the first pass, sums the
+// loss over the rows.
+__global__ void __launch_bounds__(256) upd_du_sum_kernel(UpdateArgs u, int c0, int nb, const float *counts) {
     __shared__ float part[16][17];
+    if ((int)blockIdx.x == u.n) {  // one more workgroup in the first pass
+        if (threadIdx.x < 64) upd_loss(u, counts);
+        return;
+    }
     const int i = blockIdx.x, c = threadIdx.x & 15, j = threadIdx.x >> 4;
     const int per = (nb + 15) / 16, b0 = min(nb, j * per), b1 = min(nb, b0 + per);
     float t = 0.f;
@@ -1565,8 +1558,8 @@ __global__ void __launch_bounds__(256) upd_du_sum_kernel(UpdateArgs u, int c0, i
 }
 
 // dB[c][k] = sum_i du[i][c] h[i][k] for the 16 ranks c0 .. c0 + 15: lane = k (64 per wave); per
-// block of 256 rows the block's du slice goes to LDS and wave w of eight takes rows 32 w .. 32 w +
-// 31 of the block, eight rows' loads of h in flight.  The eight waves' sums are added in order
+// block of up to 256 rows the block's du slice goes to LDS and the eight waves take an eighth of its
+// rows each, eight rows' loads of h in flight.  The eight waves' sums are added in order
 // through LDS.  h is read once per pass.
 template <DType T>
 __global__ void __launch_bounds__(512) upd_dB_kernel(UpdateArgs u, int c0) {
@@ -1582,7 +1575,8 @@ __global__ void __launch_bounds__(512) upd_dB_kernel(UpdateArgs u, int c0) {
         __syncthreads();  // every wave is done with the previous block's slice
         stage_rank_slice(ds, u.du, u.n, u.rank, rb, c0, 512);
         __syncthreads();
-        const int i0 = min(u.n, rb + 32 * w), i1 = min(u.n, i0 + 32);
+        const int rpw = (min(256, u.n - rb) + 7) / 8;  // rows per wave
+        const int i0 = min(u.n, rb + rpw * w), i1 = min(u.n, i0 + rpw);
         for (int ib = i0; ib < i1; ib += 8) {
             float hv[8];
 #pragma unroll
@@ -1619,38 +1613,34 @@ __global__ void __launch_bounds__(512) upd_dB_kernel(UpdateArgs u, int c0) {
 
 void launch_update_forward(DType t, const UpdateArgs &u, hipStream_t s) {
     float *counts = u.loss_out + 12;
-    upd_counts_kernel<<<1, 64, 0, s>>>(u.r, u.fresh, u.n, counts);
-    launch_lora_u(t, u.Hh, u.Bm, u.n, u.d, u.rank, u.u, s);
-    for (int r0 = 0; r0 < u.n; r0 += 256) {
-        const int rows = min(256, u.n - r0);
-        launch_gather_fm(t, u.Hh, false, 1, r0, rows, u.d, u.xfm, s);
-        const float *ur = u.u + (size_t)r0 * u.rank;
-        float *Zr = u.Z + (size_t)r0 * u.V;
-        GemmArgs g{};
-        g.W = u.W;
-        g.X = u.xfm;
-        g.M = rows;
-        g.N = u.V;
-        g.K = u.d;
-        g.Z = Zr;
-        g.lora_A = u.A;
-        g.lora_u = ur;
-        g.r = u.rank;
-        g.gamma = u.gamma;
-        launch_gemm_rows(t, EPI_LOGITS, g, s);
-    }
+    const int prep = u.n * (u.rank + 1) + 1;
+    if (t == DType::BF16)
+        upd_prep_kernel<DType::BF16><<<prep, 256, 0, s>>>(u, counts);
+    else
+        upd_prep_kernel<DType::F32><<<prep, 256, 0, s>>>(u, counts);
+    GemmArgs g{};
+    g.W = u.W;
+    g.X = u.xfm;
+    g.M = u.n;
+    g.N = u.V;
+    g.K = u.d;
+    g.Z = u.Z;
+    g.lora_A = u.A;
+    g.lora_u = u.u;
+    g.r = u.rank;
+    g.gamma = u.gamma;
+    launch_gemm_rows(t, EPI_LOGITS, g, s);
     if (u.V <= 4096)
         upd_rows_kernel<4><<<u.n, 1024, 0, s>>>(u, counts);
     else
         upd_rows_kernel<32><<<u.n, 1024, 0, s>>>(u, counts);
-    upd_loss_kernel<<<1, 64, 0, s>>>(u, counts);
 }
 
 void launch_update_backward(DType t, const UpdateArgs &u, hipStream_t s) {
     const int nb = grad_parts(u.V);
     for (int c0 = 0; c0 < u.rank; c0 += 16) {  // 16 ranks per pass over g
         upd_grad_kernel<<<nb, 64 * kGradWaves, 0, s>>>(u, c0);
-        upd_du_sum_kernel<<<u.n, 256, 0, s>>>(u, c0, nb);
+        upd_du_sum_kernel<<<u.n + (c0 == 0), 256, 0, s>>>(u, c0, nb, u.loss_out + 12);
     }
     for (int c0 = 0; c0 < u.rank; c0 += 16) {
         if (t == DType::BF16)
@@ -1660,22 +1650,35 @@ void launch_update_backward(DType t, const UpdateArgs &u, hipStream_t s) {
     }
 }
 
-__global__ void adam_kernel(float *p, const float *g, float *m, float *v, int n, float lr, float b1, float b2, float eps,
-                            float c1, float c2) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
+// The end of an update in one launch (as two Adam launches, two gradient copies and the flag reset:
+// 20 us of launches for 4 us of memory traffic): thread i takes element i of A_s, then of B_s, then
+// clears ring flag i - nA - nB.
+__global__ void __launch_bounds__(256) upd_finish_kernel(FinishArgs f) {
+    long i = (long)blockIdx.x * 256 + threadIdx.x;
+    const bool isA = i < f.nA;
+    if (!isA) i -= f.nA;
+    if (!isA && i >= f.nB) {
+        i -= f.nB;
+        if (i < f.ring_rows) f.fresh[i] = 0;
+        return;
+    }
+    const float gi = (isA ? f.gA : f.gB)[i];
+    float *out = isA ? f.outA : f.outB;
+    if (out != nullptr) out[i] = gi;
+    if (f.lr == 0.f) return;
+    float *m = isA ? f.mA : f.mB, *v = isA ? f.vA : f.vB, *p = isA ? f.A : f.B;
+    const float mi = f.b1 * m[i] + (1.f - f.b1) * gi;
+    const float vi = f.b2 * v[i] + (1.f - f.b2) * gi * gi;
     m[i] = mi;
     v[i] = vi;
-    p[i] = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    p[i] = p[i] - f.lr * (mi / f.c1) / (sqrtf(vi / f.c2) + f.eps);
 }
 
-void launch_adam(float *p, const float *g, float *m, float *v, int n, float lr, float b1, float b2, float eps, int step,
-                 hipStream_t s) {
-    const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
-    adam_kernel<<<(n + 255) / 256, 256, 0, s>>>(p, g, m, v, n, lr, b1, b2, eps, c1, c2);
+void launch_update_finish(FinishArgs f, int step, hipStream_t s) {
+    f.c1 = 1.f - powf(f.b1, (float)step);
+    f.c2 = 1.f - powf(f.b2, (float)step);
+    const long n = f.nA + f.nB + f.ring_rows;
+    upd_finish_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(f);
 }
 
 // ------------------------------------------------------------------------------------------
