@@ -674,7 +674,7 @@ __device__ __forceinline__ void merge_row(const AttnArgs &a, int m, int h, int n
     store_row<T, HD>(a, m, h, lane, o, L);
 }
 
-constexpr long kAttnLargeGrid = 2048;  // chunk-waves from which the merge takes its own launch
+constexpr long kAttnLargeGrid = 1024;  // chunk-waves from which the merge takes its own launch
 
 // One wave's 64-key chunk ch of (sequence b, kv head kvh), nk of its keys in the cache.
 // Keys are cut into 64-position chunks at absolute positions; the query rows that read this kv
@@ -987,6 +987,49 @@ __global__ void __launch_bounds__(64 * WPB, (ONE && T == DType::BF16) ? 3 : 1) a
     }
 }
 
+// The whole attention of short contexts (at most WPB chunks, at most 16 query rows per kv head) in one
+// workgroup per (sequence, kv head): wave w takes chunk w, the partials stay in LDS, and the waves merge
+// the rows there.  Same chunk and merge arithmetic as attn_kernel (merge_fold over eight chunks, those
+// past the row's repeated with weight zero).  What it saves is the handoff: at one row the partials'
+// way through memory, the counter and the reload took about half of attn_kernel's time, at more than
+// four rows a launch of its own.  Bound by the latency of one chain: queries and keys, then values.
+template <DType T, int HD, int WPB>
+__global__ void __launch_bounds__(64 * WPB) attn_local_kernel(AttnArgs a) {
+    typedef typename St<T>::type E;
+    constexpr int PST = CK + 16 / (int)sizeof(E), PER = HD / 64, NB = 8;
+    static_assert(WPB <= NB, "one merge group");
+    __shared__ __align__(16) E Ps[WPB][16][PST];
+    __shared__ __align__(16) float po[WPB][16][HD];
+    __shared__ float2 ml[WPB][16];
+    const int kvh = blockIdx.x, b = blockIdx.y;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int len0 = a.lens[b] + a.pos_off, pmax = len0 + a.c - 1, nch = pmax / CK + 1;
+    const int G = a.n_heads / a.n_kv, R = a.c * G;
+    if (w < nch) {  // uniform across the wave; nch <= WPB
+        auto sink = [&](int r, const float (&v)[HD / 16], bool stats, float mx, float sm) {
+            float *o = &po[w][r][(lane & 15) * (HD / 16)];
+#pragma unroll
+            for (int q = 0; q < HD / 16; q += 4) *(float4 *)(o + q) = make_float4(v[q], v[q + 1], v[q + 2], v[q + 3]);
+            if (stats) ml[w][r] = make_float2(mx, sm);
+        };
+        attn_chunk1<T, HD>(a, b, kvh, w, len0, min(CK, pmax + 1 - w * CK), Ps[w], sink);
+    }
+    __syncthreads();
+    for (int row = w; row < R; row += WPB) {
+        const int i = row / G, gi = row - i * G, cn = (len0 + i) / CK + 1;  // cn <= nch
+        const float2 st = ml[min(lane, cn - 1)][row];
+        float ov[NB][PER], Mr = -INFINITY, L = 0.f, o[PER];
+#pragma unroll
+        for (int u = 0; u < NB; ++u)
+#pragma unroll
+            for (int q = 0; q < PER; ++q) ov[u][q] = po[min(u, cn - 1)][row][PER * lane + q];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) o[q] = 0.f;
+        merge_fold<HD, NB>(st.x, st.y, ov, cn, lane, Mr, L, o);
+        store_row<T, HD>(a, b * a.c + i, kvh * G + gi, lane, o, L);
+    }
+}
+
 // The merge as a launch of its own: one wave per (query row, head), all at once.
 template <DType T, int HD>
 __global__ void __launch_bounds__(256) attn_merge_kernel(AttnArgs a) {
@@ -1010,7 +1053,20 @@ static void launch_attention_t(const AttnArgs &a, hipStream_t s, const LaunchEve
     // otherwise every workgroup would wait for its partial stores before counting itself done,
     // and the last merges would run at the kernel's tail, each wave merging several rows one
     // after another (6 rows: 17.1 -> 16.0 us, 20 rows: 18.6 -> 15.7 us with the second launch).
+    // The large grid starts at 1024 chunk-waves: four 7B sequences of 440-700 positions (1536) step in
+    // 549 us with the second launch against 588, one 13B sequence of 1024 (800) in 2538 against 2531,
+    // one 7B sequence of 512 (384) the same either way.
     const int rows = a.c * (a.n_heads / a.n_kv);
+    // Contexts of up to 256 and 512 positions with one query tile stay in one workgroup per head (tiny
+    // fp32 step of four sequences 462 -> 450 us, 1B step at 260 positions 2606 -> 2597 us).
+    if (rows <= 16 && a.n_chunks <= 4) {
+        launch_timed(attn_local_kernel<T, HD, 4>, dim3(a.n_kv, a.B), dim3(256), s, ev, a);
+        return;
+    }
+    if (rows <= 16 && a.n_chunks <= 8) {
+        launch_timed(attn_local_kernel<T, HD, 8>, dim3(a.n_kv, a.B), dim3(512), s, ev, a);
+        return;
+    }
     const long waves = (long)a.n_chunks * a.n_kv * a.B;
     if (waves >= kAttnLargeGrid || rows > 4) {
         const int all_rows = a.B * a.c * a.n_heads;
