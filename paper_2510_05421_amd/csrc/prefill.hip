@@ -357,10 +357,16 @@ __device__ __forceinline__ void rows_epilogue(const GemmArgs &a, int t0, int g0,
 // need, go through an LDS ring of NS stages of CPS chunks by direct-to-LDS copies, one barrier per
 // stage.  Staging both operands in LDS, as the kernel before did, needed 172 bytes of LDS traffic per
 // clock at full MFMA rate against the 128 it has; this split needs 80.
-// 128 x 256 tiles of eight waves (64 accumulators, 124 registers) leave room for two workgroups on a
-// compute unit, so one's epilogue runs under the other's MFMAs.  7B shapes, 2048 rows, against the
-// kernel before: out-proj 85 -> 74 us, down 181 -> 157, gate/up 345 -> 293, QKV 212 -> 172 (934-1260
-// TFLOP/s); 8192 rows 350 -> 271, 784 -> 596, 1315 -> 1102, 855 -> 669 (1014-1340 TFLOP/s).
+// 128 x 256 tiles of four waves, four feature tiles each (128 accumulators, 236 registers), leave room
+// for two workgroups on a compute unit, so one's epilogue runs under the other's MFMAs; each fragment
+// read from LDS feeds four MFMAs.  With PIPE the fragments of the next chunk are read before the
+// products of the current one, across the stage barrier too: read two at a time just before their use,
+// as the compiler places them, every pair stalled both waves of a SIMD for the LDS latency.  7B shapes,
+// 8192 rows, in sequence and so at the clock this load settles at: gate/up 1212 -> 1189 us, QKV 778 ->
+// 741, out-proj and down 985 -> 929 against eight waves of two feature tiles without PIPE; 512 rows: QKV
+// 78 -> 73, out-proj and down 128 -> 117.  256 x 256 tiles (1254, 769, 968 us) and more bytes in flight
+// change little: at 1240 TFLOP/s the MFMA rate under the power limit is near (the library's 8192 cubed
+// product reaches 1470).
 // Workgroups are numbered so that each XCD (workgroup id mod 8) takes a contiguous range of tiles,
 // in strips of kStrip feature blocks with the token tile major: the tiles that run together on an
 // XCD form a near-square, which reads the fewest bytes into its L2 (gate/up, 8192 rows: 1167 ->
@@ -383,11 +389,12 @@ __device__ __forceinline__ void add_parts(f32x4 (&acc)[N][RT][XG]) {
                 acc[0][t][g] = (acc[0][t][g] + acc[1][t][g]) + (acc[2][t][g] + acc[3][t][g]);
 }
 
-template <DType T, int EPI, int WV, int RT, int XG, int CPS, int NS, int WD, int MINW, int NACC>
+// CPS chunks per stage, NS stages of the ring, WD chunks of weights in flight.
+template <DType T, int EPI, int WV, int RT, int XG, int CPS, int NS, int WD, int MINW, bool PIPE, int NACC>
 __global__ void __launch_bounds__(64 * WV, MINW) gemm_rows_kernel(GemmArgs a, int tok_tiles, int blocks, int total) {
     constexpr int PX = CPS * XG / WV;        // copies per wave and stage
     constexpr int UN = WD > CPS ? WD / CPS : 1;  // stages per turn of the weight ring
-    static_assert(PX * WV == CPS * XG && UN * CPS == WD && WD % NACC == 0, "stage and ring shapes");
+    static_assert(PX * WV == CPS * XG && UN * CPS == WD && WD % NACC == 0 && (!PIPE || WD % 2 == 0), "stage and ring shapes");
     __shared__ __align__(1024) uint4 ring[NS][CPS * XG][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int KT = a.K / ((T == DType::BF16) ? 32 : 16), NT = a.N / 16, NG = (a.M + 15) / 16;
@@ -433,40 +440,89 @@ __global__ void __launch_bounds__(64 * WV, MINW) gemm_rows_kernel(GemmArgs a, in
     for (int st = 0; st < NS - 1; ++st) copy_stage(st, st);
 #pragma unroll
     for (int k = 0; k < WD; ++k) load_w(k, w[k]);
-    // Operations issued after the copies of the stage about to be read, NS - 1 stages ago.  In the
-    // first stage all weight loads so far came after all copies; the loop's bound covers that too
-    // when it is no larger, so the first stage takes the smaller of the two.
+    // Operations issued after the copies of the stage about to be read: those went out when stage
+    // NS - 1 before it was about to be read, and NS - 2 stages' copies and (NS - 1) CPS chunks' weights
+    // after them.  The first NS - 1 stages' copies all came before the first weight loads, so for them
+    // the count starts at kFirst; waiting for the smaller of the two serves every stage.
     constexpr int kLoop = (NS - 1) * CPS * RT + (NS - 2) * PX, kFirst = WD * RT + (NS - 2) * PX;
     constexpr int kYoung = (kLoop < kFirst ? kLoop : kFirst) < 63 ? (kLoop < kFirst ? kLoop : kFirst) : 63;
     const int KS = KT / CPS;  // KT is a multiple of CPS
-    int st = 0;
-    for (int s0 = 0; s0 < KS; s0 += UN) {
+    if constexpr (PIPE) {
+        auto read_x = [&](int st, int c, uint4 (&xf)[XG]) {
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int s = s0 + u;
-            if (UN > 1 && s >= KS) break;  // uniform
-            // this wave's copies of stage s have landed and its reads of stage s - 1 have returned;
-            // past the barrier that holds for every wave, so stage s can be read and the slot of
-            // stage s - 1 overwritten
-            wait_mem<kYoung, true>();
-            barrier();
-            copy_stage(st == 0 ? NS - 1 : st - 1, s + NS - 1);
-            const uint4 *b = &ring[st][0][lane];
+            for (int g = 0; g < XG; ++g) xf[g] = ring[st][c * XG + g][lane];
+        };
+        uint4 x[2][XG];  // token fragments: the chunk being multiplied and the one after it
+        int st = 0;
+        wait_mem<kYoung, true>();
+        barrier();
+        copy_stage(NS - 1, NS - 1);
+        read_x(0, 0, x[0]);
+        for (int s0 = 0; s0 < KS; s0 += UN) {
 #pragma unroll
-            for (int c = 0; c < CPS; ++c) {
-                uint4(&wf)[RT] = w[(u * CPS + c) % WD];
+            for (int u = 0; u < UN; ++u) {
+                const int s = s0 + u;
+                if (UN > 1 && s >= KS) break;  // uniform
 #pragma unroll
-                for (int g = 0; g < XG; ++g) {
-                    const uint4 xf = b[(c * XG + g) * 64];
-#pragma unroll
-                    for (int t = 0; t < RT; ++t) {
-                        f32x4 &o = acc[(u * CPS + c) % NACC][t][g];
-                        o = St<T>::mma(wf[t], xf, o);
+                for (int c = 0; c < CPS; ++c) {
+                    const int q = u * CPS + c;
+                    if (c + 1 < CPS) {
+                        read_x(st, c + 1, x[(q + 1) & 1]);
+                    } else {
+                        // this wave's copies of stage s + 1 have landed and its reads of stage s have
+                        // returned; past the barrier that holds for every wave, so stage s + 1 can be read
+                        // and the slot of stage s overwritten (stages past the end repeat the last chunk
+                        // and are not multiplied)
+                        const int next = st + 1 == NS ? 0 : st + 1;
+                        wait_mem<kYoung, true>();
+                        barrier();
+                        copy_stage(st, s + NS);
+                        read_x(next, 0, x[(q + 1) & 1]);
+                        st = next;
                     }
+                    __builtin_amdgcn_sched_barrier(0);  // the reads above go out before these products
+                    uint4(&wf)[RT] = w[q % WD];
+#pragma unroll
+                    for (int g = 0; g < XG; ++g)
+#pragma unroll
+                        for (int t = 0; t < RT; ++t) {
+                            f32x4 &o = acc[q % NACC][t][g];
+                            o = St<T>::mma(wf[t], x[q & 1][g], o);
+                        }
+                    load_w(s * CPS + c + WD, wf);
                 }
-                load_w(s * CPS + c + WD, wf);
             }
-            st = st + 1 == NS ? 0 : st + 1;
+        }
+    } else {
+        int st = 0;
+        for (int s0 = 0; s0 < KS; s0 += UN) {
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int s = s0 + u;
+                if (UN > 1 && s >= KS) break;  // uniform
+                // this wave's copies of stage s have landed and its reads of stage s - 1 have returned;
+                // past the barrier that holds for every wave, so stage s can be read and the slot of
+                // stage s - 1 overwritten
+                wait_mem<kYoung, true>();
+                barrier();
+                copy_stage(st == 0 ? NS - 1 : st - 1, s + NS - 1);
+                const uint4 *b = &ring[st][0][lane];
+#pragma unroll
+                for (int c = 0; c < CPS; ++c) {
+                    uint4(&wf)[RT] = w[(u * CPS + c) % WD];
+#pragma unroll
+                    for (int g = 0; g < XG; ++g) {
+                        const uint4 xf = b[(c * XG + g) * 64];
+#pragma unroll
+                        for (int t = 0; t < RT; ++t) {
+                            f32x4 &o = acc[(u * CPS + c) % NACC][t][g];
+                            o = St<T>::mma(wf[t], xf, o);
+                        }
+                    }
+                    load_w(s * CPS + c + WD, wf);
+                }
+                st = st + 1 == NS ? 0 : st + 1;
+            }
         }
     }
     wait_mem<0, true>();  // no copy may land after the workgroup has given its LDS back
@@ -557,12 +613,12 @@ void launch_ev(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t s, const
         kernel<<<grid, block, 0, s>>>(args...);
 }
 
-template <DType T, int EPI, int WV, int RT, int XG, int CPS, int NS, int WD, int MINW, int NACC = 1>
+template <DType T, int EPI, int WV, int RT, int XG, int CPS, int NS, int WD, int MINW, bool PIPE, int NACC = 1>
 void launch_rows(const GemmArgs &a, hipStream_t s, const LaunchEvents &ev) {
     const int tok = (a.M + 16 * XG - 1) / (16 * XG), blk = (a.N / 16 + RT * WV - 1) / (RT * WV), total = tok * blk;
     if (a.ss_in != nullptr)
         rms_rows_kernel<<<(a.M + 15) / 16, 64, 0, s>>>(a.ss_in, a.ld_ss_in, a.K / 16, a.K, a.eps, a.M, a.sinv_rows);
-    launch_ev(gemm_rows_kernel<T, EPI, WV, RT, XG, CPS, NS, WD, MINW, NACC>, dim3(8 * ((total + 7) / 8)), dim3(64 * WV),
+    launch_ev(gemm_rows_kernel<T, EPI, WV, RT, XG, CPS, NS, WD, MINW, PIPE, NACC>, dim3(8 * ((total + 7) / 8)), dim3(64 * WV),
               s, ev, a, tok, blk, total);
 }
 
@@ -582,7 +638,10 @@ void launch_few(const GemmArgs &a, hipStream_t s, const LaunchEvents &ev) {
 // workgroups of 128 x 256, 34 us as 256 of 64 x 128; gate/up there 104 us as 344 of 128 x 256, 110 us
 // as 688 of 128 x 128).  A grid of at most one workgroup per compute unit takes the whole unit: deeper
 // rings, 256 registers (out-proj at 2048 rows 82 -> 72 us, QKV at 512 rows 84 -> 73 us; with two
-// workgroups per unit that costs 20%: gate/up 104 -> 123 us).  When not even 64 x 64 tiles fill the
+// workgroups per unit that costs 20%: gate/up 104 -> 123 us).  PIPE where its second set of fragments
+// fits and was the faster: eight waves of one feature tile keep the plain loop (1024 rows, 7B: 2104 us a
+// prefill of four layers, 2168 as four piped waves of two tiles; 200 rows 1043 against 1188), as do the
+// 64 x 64 tiles (1B, 37 rows: 1111 against 1144 us).  When not even 64 x 64 tiles fill the
 // chip, a wave per tile and four groups again (1B down at 200 rows 45 -> 38 us).  A K of an odd number
 // of chunks takes one-chunk stages.
 template <DType T, int EPI>
@@ -592,7 +651,7 @@ void gemm_rows_t(const GemmArgs &a, hipStream_t s, const LaunchEvents &ev) {
     const long want = (long)cu * 3 / 4;
     auto wgs = [&](int rows, int feats) { return (long)((a.M + rows - 1) / rows) * ((a.N + feats - 1) / feats); };
     if (NG == 1) return launch_few<T, EPI, 1, 24, 12>(a, s, ev);
-    if (a.M <= 64 && NT > 2 * cu && KT % 2 == 0) return launch_rows<T, EPI, 4, 1, 4, 2, 4, 8, 2, NACC>(a, s, ev);
+    if (a.M <= 64 && NT > 2 * cu && KT % 2 == 0) return launch_rows<T, EPI, 4, 1, 4, 2, 4, 8, 2, false, NACC>(a, s, ev);
     if (a.M <= 64 || wgs(64, 64) < want) {
         const int xg = (int)std::min<long>(4, std::max<long>(1, (long)NT * NG / cu));
         if (xg == 1) return launch_few<T, EPI, 1, 24, 12>(a, s, ev);
@@ -600,13 +659,14 @@ void gemm_rows_t(const GemmArgs &a, hipStream_t s, const LaunchEvents &ev) {
         if (NG == 3) return launch_few<T, EPI, 3, 16, 8>(a, s, ev);
         return launch_few<T, EPI, 4, 16, 8>(a, s, ev);
     }
-    if (KT % 2) return launch_rows<T, EPI, 8, 2, 8, 1, 7, 2, 4>(a, s, ev);
-    if (wgs(128, 256) > cu) return launch_rows<T, EPI, 8, 2, 8, 2, 4, 4, 4>(a, s, ev);
-    if (wgs(128, 256) >= want) return launch_rows<T, EPI, 8, 2, 8, 2, 8, 16, 2>(a, s, ev);
-    if (wgs(128, 128) > cu) return launch_rows<T, EPI, 8, 1, 8, 2, 4, 8, 4>(a, s, ev);
-    if (wgs(128, 128) >= want) return launch_rows<T, EPI, 8, 1, 8, 2, 8, 16, 2>(a, s, ev);
-    if (wgs(64, 128) >= want) return launch_rows<T, EPI, 8, 1, 4, 2, 6, 16, 4>(a, s, ev);
-    return launch_rows<T, EPI, 4, 1, 4, 2, 4, 8, 2>(a, s, ev);
+    if (KT % 2) return launch_rows<T, EPI, 8, 2, 8, 1, 7, 2, 4, false>(a, s, ev);
+    if (wgs(128, 256) > cu) return launch_rows<T, EPI, 4, 4, 8, 2, 4, 2, 2, true>(a, s, ev);
+    if (wgs(128, 256) >= want) return launch_rows<T, EPI, 8, 2, 8, 2, 8, 8, 2, true>(a, s, ev);
+    if (wgs(128, 128) > cu) return launch_rows<T, EPI, 8, 1, 8, 2, 4, 8, 4, false>(a, s, ev);
+    if (wgs(128, 128) >= want) return launch_rows<T, EPI, 8, 1, 8, 2, 8, 16, 2, false>(a, s, ev);
+    if (wgs(64, 128) >= want && KT % 4 == 0) return launch_rows<T, EPI, 4, 2, 4, 4, 4, 8, 2, true>(a, s, ev);
+    if (wgs(64, 128) >= want) return launch_rows<T, EPI, 8, 1, 4, 2, 6, 16, 4, false>(a, s, ev);
+    return launch_rows<T, EPI, 4, 1, 4, 2, 4, 8, 2, false>(a, s, ev);
 }
 
 template <DType T>

@@ -23,6 +23,8 @@ SHAPES = {
     "odd": BASE.replace(name="odd", d_model=96, n_heads=2, n_kv_heads=1, head_dim=64, ffn_dim=160, bf16=True),
     # 1152 gate/up tiles, head dim 128
     "wide": BASE.replace(name="wide", d_model=512, n_heads=4, n_kv_heads=4, head_dim=128, ffn_dim=9216, bf16=True),
+    # the same width over 10 chunks of K, head dim 64
+    "wide10": BASE.replace(name="wide10", d_model=320, n_heads=5, n_kv_heads=5, head_dim=64, ffn_dim=9216, bf16=True),
     # fp32, K of 3 and 5 chunks, head dim 64; and head dim 128
     "fp32": BASE.replace(name="fp32", d_model=48, n_heads=1, n_kv_heads=1, head_dim=64, ffn_dim=80),
     "fp32_128": BASE.replace(name="fp32_128", d_model=256, n_heads=6, n_kv_heads=2, head_dim=128, ffn_dim=512),
@@ -32,6 +34,7 @@ CASES = [
     ("odd", [3000, 2700, 3001]),
     ("wide", [9]), ("wide", [33]), ("wide", [64]), ("wide", [65, 2]), ("wide", [200]), ("wide", [300, 7]),
     ("wide", [65, 255, 280]), ("wide", [1100, 63, 128]), ("wide", [2100, 2100, 1999, 17]),
+    ("wide10", [65, 2]), ("wide10", [255, 65]), ("wide10", [1100]),
     ("fp32", [5]), ("fp32", [33, 31]), ("fp32", [70, 33]), ("fp32", [520, 300]),
     ("fp32_128", [7]), ("fp32_128", [129, 64, 1]), ("fp32_128", [900, 700, 450]),
 ]
