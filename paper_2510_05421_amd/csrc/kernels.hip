@@ -1465,36 +1465,6 @@ __device__ __forceinline__ void upd_loss(const UpdateArgs &u, const float *count
     u.loss_out[8] = counts[3];
 }
 
-// Sums p[0..15] over the 64 lanes of the wave, all sixteen at once: four halving steps each hand
-// half of the carried values to the lane 32, 16, 8 apart and then to the mirror lane of the
-// 8-lane half row (lane ^ 7), keeping the other half; two plain steps add within the quad.  Lane l
-// returns the total of value l >> 2.  The tree is fixed, so the sums are deterministic.  The first
-// two steps use v_permlane32_swap / v_permlane16_swap: swapping the upper half-wave (odd rows) of
-// value k with the lower half-wave (even rows) of value k + 8 (k + 4) leaves each lane its own and
-// its partner's share of the value it keeps, in two registers that one add combines.
-__device__ __forceinline__ float swap_sum32(float lo, float hi) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float swap_sum16(float lo, float hi) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float transpose_sum16(const float (&p)[16], int lane) {
-    const bool h8 = lane & 8, h4 = lane & 4;
-    float q[8], r[4], t[2];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) q[k] = swap_sum32(p[k], p[k + 8]);  // lanes < 32: value k, else k + 8
-#pragma unroll
-    for (int k = 0; k < 4; ++k) r[k] = swap_sum16(q[k], q[k + 4]);  // even rows: k, odd rows: k + 4
-#pragma unroll
-    for (int k = 0; k < 2; ++k) t[k] = (h8 ? r[k + 2] : r[k]) + dpp_f32<0x128>(h8 ? r[k] : r[k + 2]);  // row_ror 8
-    float v = (h4 ? t[1] : t[0]) + dpp_f32<0x141>(h4 ? t[0] : t[1]);  // half-row mirror
-    v += dpp_f32<0xB1>(v);
-    v += dpp_f32<0x4E>(v);
-    return v;
-}
-
 // Rows rb .. rb + 255 of the ranks c0 .. c0 + 15 of a row-major [n][rank] matrix into LDS, 16
 // floats per row, zero past the rank and past n (so the readers need no guards).
 __device__ __forceinline__ void stage_rank_slice(float (&dst)[256][16], const float *src, int n, int rank, int rb,
@@ -1506,78 +1476,89 @@ __device__ __forceinline__ void stage_rank_slice(float (&dst)[256][16], const fl
 }
 
 // dA[v][c] = gamma sum_i g[i][v] u[i][c] and du[i][c] = gamma sum_v A_s[v][c] g[i][v], g = dL/dz
-// (the rows of Z after upd_rows_kernel), in one pass over g for the 16 ranks c0 .. c0 + 15.  A
-// workgroup takes kGradV = 128 vocabulary entries, two per lane (v0 = 128 b + 2 l, v0 + 1), and
-// every row: per block of up to 256 rows, the block's u slice goes to LDS and the eight waves take an
-// eighth of its rows each (48 rows in blocks of 32 per wave left six waves idle: 20 us), eight rows'
-// loads of g in flight.  A lane keeps its two entries' rows
-// of A_s and their 16 dA sums (its rows in order; the eight waves are then added in order through
-// LDS).  Per row it forms the two entries' share of du for the 16 ranks, which transpose_sum16
-// reduces over the wave, and the workgroup's share goes to du_part[b][i][16]; upd_du_sum_kernel
-// adds the workgroups' shares.  g and A_s are each read once (V even, as every vocabulary here
-// is a multiple of 16).
+// (the rows of Z after upd_rows_kernel), for the 16 ranks c0 .. c0 + 15: two contractions over g on
+// fp32 MFMAs (16 ranks x 16 columns, four terms of the sum each).  A workgroup takes kGradV = 128
+// vocabulary entries; wave w takes the 16-row blocks w, w + 8, ...  A block of g is read twice, once
+// with the rows and once with the vocabulary as the MFMA's summed index, both times 16 bytes a lane
+// and all in flight together; the second reading hits the caches, so memory still carries g once.  A
+// wave keeps its dA sums over its blocks (the eight waves are added in order through LDS); a block's
+// du sums go to du_part[b][i][16], and upd_du_sum_kernel adds the workgroups' shares.  V is a multiple
+// of 16, as every vocabulary here.  Bound by the latency of one block's loads and then by memory; with
+// vector fmas and a 64-lane reduction per row it was bound by those (28.9 us at 256 rows of V = 32000; the
+// whole update there, at d = 5120, 258 -> 247 us; 48 rows at d = 4096, 177 -> 175).
 constexpr int kGradWaves = 8;
 
 __global__ void __launch_bounds__(64 * kGradWaves) upd_grad_kernel(UpdateArgs u, int c0) {
     __shared__ float red[kGradWaves][kGradV][17];
-    __shared__ __align__(16) float us[256][16];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int b = blockIdx.x, v0 = b * kGradV + 2 * lane;
-    const int rc = min(16, u.rank - c0);
-    const bool in0 = v0 < u.V, in1 = v0 + 1 < u.V;
-    const size_t vc = (size_t)min(v0, u.V - 2);  // lanes past V read an in-range pair, weighted 0
-    float a0[16], a1[16], d0[16], d1[16];
+    const int l16 = lane & 15, q4 = lane >> 4;
+    const int b = blockIdx.x, v0 = b * kGradV;
+    const int rc = min(16, u.rank - c0), cc = c0 + min(l16, rc - 1);
+    constexpr int VB = kGradV / 16, VH = kGradV / 64;
+    // A_s[v][c0 + l16] of the lane's summed entries v = v0 + 16 m + 4 q4 + j
+    float as[VB][4];
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-        const int cc = c0 + min(c, rc - 1);  // in range even where the value is not used
-        a0[c] = (in0 && c < rc) ? u.A[(size_t)min(v0, u.V - 1) * u.rank + cc] : 0.f;
-        a1[c] = (in1 && c < rc) ? u.A[(size_t)min(v0 + 1, u.V - 1) * u.rank + cc] : 0.f;
-        d0[c] = 0.f;
-        d1[c] = 0.f;
-    }
-    for (int rb = 0; rb < u.n; rb += 256) {
-        __syncthreads();  // every wave is done with the previous block's slice
-        stage_rank_slice(us, u.u, u.n, u.rank, rb, c0, 64 * kGradWaves);
-        __syncthreads();
-        const int rpw = (min(256, u.n - rb) + kGradWaves - 1) / kGradWaves;  // rows per wave
-        const int i0 = min(u.n, rb + rpw * w), i1 = min(u.n, i0 + rpw);
-        for (int ib = i0; ib < i1; ib += 8) {
-            float2 g2[8];
+    for (int m = 0; m < VB; ++m)
 #pragma unroll
-            for (int k = 0; k < 8; ++k) g2[k] = *(const float2 *)(u.Z + (size_t)min(ib + k, i1 - 1) * u.V + vc);
+        for (int j = 0; j < 4; ++j) {
+            const int v = v0 + 16 * m + 4 * q4 + j;
+            const float t = u.A[(size_t)min(v, u.V - 1) * u.rank + cc];
+            as[m][j] = (v < u.V && l16 < rc) ? t : 0.f;
+        }
+    f32x4 dA[VH][4];  // [h][t][j]: rank 4 q4 + j, entry v0 + 64 h + 4 l16 + t
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int i = ib + k;
-                if (i < i1) {  // uniform; a guard, not a break, so the loop unrolls
-                    const float g0 = in0 ? g2[k].x : 0.f, g1 = in1 ? g2[k].y : 0.f;
-                    const float4 *ur = (const float4 *)us[i - rb];
-                    float uc[16];
+    for (int h = 0; h < VH; ++h)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float4 t = ur[q];
-                        uc[4 * q] = t.x;
-                        uc[4 * q + 1] = t.y;
-                        uc[4 * q + 2] = t.z;
-                        uc[4 * q + 3] = t.w;
-                    }
-                    float p[16];
+        for (int t = 0; t < 4; ++t) dA[h][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int ib = 16 * w; ib < u.n; ib += 16 * kGradWaves) {
+        float4 gr[4][VH], gv[VB];  // rows ib + 4 s + q4, entries 64 h + 4 l16 ..; row ib + l16, entries 16 m + 4 q4 ..
+        float uv[4];
 #pragma unroll
-                    for (int c = 0; c < 16; ++c) {
-                        d0[c] += g0 * uc[c];
-                        d1[c] += g1 * uc[c];
-                        p[c] = a0[c] * g0 + a1[c] * g1;
-                    }
-                    const float sdu = transpose_sum16(p, lane);
-                    if ((lane & 3) == 0) u.du_part[((size_t)b * u.n + i) * 16 + (lane >> 2)] = sdu;
-                }
+        for (int s = 0; s < 4; ++s) {
+            const size_t i = (size_t)min(ib + 4 * s + q4, u.n - 1);
+#pragma unroll
+            for (int h = 0; h < VH; ++h)
+                gr[s][h] = *(const float4 *)(u.Z + i * u.V + min(v0 + 64 * h + 4 * l16, u.V - 4));
+            uv[s] = u.u[i * u.rank + cc];
+        }
+#pragma unroll
+        for (int m = 0; m < VB; ++m)
+            gv[m] = *(const float4 *)(u.Z + (size_t)min(ib + l16, u.n - 1) * u.V + min(v0 + 16 * m + 4 * q4, u.V - 4));
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const bool row = ib + 4 * s + q4 < u.n;  // rows past n enter as zeros
+            const float uc = (row && l16 < rc) ? uv[s] : 0.f;
+#pragma unroll
+            for (int h = 0; h < VH; ++h) {
+                const float4 g = gr[s][h];
+                dA[h][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(uc, row ? g.x : 0.f, dA[h][0], 0, 0, 0);
+                dA[h][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(uc, row ? g.y : 0.f, dA[h][1], 0, 0, 0);
+                dA[h][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(uc, row ? g.z : 0.f, dA[h][2], 0, 0, 0);
+                dA[h][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(uc, row ? g.w : 0.f, dA[h][3], 0, 0, 0);
             }
         }
+        f32x4 du[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) du[j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int m = 0; m < VB; ++m) {
+            const bool in = v0 + 16 * m + 4 * q4 < u.V;  // entries past V enter as zeros
+            const float4 g = gv[m];
+            du[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(as[m][0], in ? g.x : 0.f, du[0], 0, 0, 0);
+            du[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(as[m][1], in ? g.y : 0.f, du[1], 0, 0, 0);
+            du[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(as[m][2], in ? g.z : 0.f, du[2], 0, 0, 0);
+            du[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(as[m][3], in ? g.w : 0.f, du[3], 0, 0, 0);
+        }
+        const f32x4 t = (du[0] + du[1]) + (du[2] + du[3]);  // ranks 4 q4 .. + 3 of row ib + l16
+        if (ib + l16 < u.n)
+            *(float4 *)(u.du_part + ((size_t)b * u.n + ib + l16) * 16 + 4 * q4) = make_float4(t[0], t[1], t[2], t[3]);
     }
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-        red[w][2 * lane][c] = d0[c];
-        red[w][2 * lane + 1][c] = d1[c];
-    }
+    for (int h = 0; h < VH; ++h)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) red[w][64 * h + 4 * l16 + t][4 * q4 + j] = dA[h][t][j];
     __syncthreads();
     for (int e = threadIdx.x; e < kGradV * 16; e += 64 * kGradWaves) {
         const int vv = e >> 4, c = e & 15, v = b * kGradV + vv;
