@@ -192,6 +192,21 @@ __device__ __forceinline__ uint4 ld_stream(const uint4 *p) {
     return uint4{t.x, t.y, t.z, t.w};
 }
 
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
+
+__device__ __forceinline__ uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(const lds_u8 *)p; }
+
+// Copy 1 KiB from memory straight into LDS: lane l's 16 bytes from base + 16 l to LDS byte dst + 16 l
+// (base and dst wave-uniform).  Written as an instruction so that the compiler does not make every
+// later LDS read wait for all copies in flight; the kernels wait by count and a barrier before they
+// read a stage.  It has no register results, so nothing can use one early.  The compiler does not look
+// inside: m0 is named as written, and the load comes five wait states after the block begins, which is
+// what a base just written by a vector instruction (v_readfirstlane, a reloaded spill) needs.
+__device__ __forceinline__ void copy_1k(uint32_t dst, uint32_t lane16, const void *base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(lane16), "s"(base)
+                 : "memory", "m0");
+}
+
 // Agent-scope relaxed accesses: coherent across the L2 caches of all compute dies, no fence.
 __device__ __forceinline__ void st_agent(float *p, float v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

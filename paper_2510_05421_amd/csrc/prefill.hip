@@ -22,10 +22,6 @@ namespace dvi {
 
 namespace {
 
-typedef __attribute__((address_space(3))) uint8_t lds_u8;
-
-__device__ __forceinline__ uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(const lds_u8 *)p; }
-
 // Wait until at most VM vector-memory operations of this wave are in flight and (LGKM0) every LDS
 // read has returned.  gfx9 s_waitcnt immediate: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8.
 template <int VM, bool LGKM0>
@@ -37,15 +33,6 @@ __device__ __forceinline__ void wait_mem() {
 __device__ __forceinline__ void barrier() {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-}
-
-// Copy 1 KiB from memory straight into LDS: lane l's 16 bytes from base + 16 l to LDS byte dst + 16 l
-// (base and dst wave-uniform).  Written as an instruction so that the compiler does not make every
-// later LDS read wait for all copies in flight; the kernels wait by count (wait_mem) and a barrier
-// before they read a stage.  It has no register results, so nothing can use one early.
-__device__ __forceinline__ void copy_1k(uint32_t dst, uint32_t lane16, const void *base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(lane16), "s"(base)
-                 : "memory");
 }
 
 __device__ __forceinline__ float sumsq4(float a, float b, float c, float d) {
