@@ -13,6 +13,7 @@
 #include <algorithm>
 
 #include "device.h"
+#include "ring.h"
 
 // Multiplies and adds fuse only where fmaf is written: otherwise the compiler picks which product of
 // a sum to fuse separately in every launch shape's instance, and a row would differ in its last bit.
@@ -427,12 +428,7 @@ __global__ void __launch_bounds__(64 * WV, MINW) gemm_rows_kernel(GemmArgs a, in
     for (int st = 0; st < NS - 1; ++st) copy_stage(st, st);
 #pragma unroll
     for (int k = 0; k < WD; ++k) load_w(k, w[k]);
-    // Operations issued after the copies of the stage about to be read: those went out when stage
-    // NS - 1 before it was about to be read, and NS - 2 stages' copies and (NS - 1) CPS chunks' weights
-    // after them.  The first NS - 1 stages' copies all came before the first weight loads, so for them
-    // the count starts at kFirst; waiting for the smaller of the two serves every stage.
-    constexpr int kLoop = (NS - 1) * CPS * RT + (NS - 2) * PX, kFirst = WD * RT + (NS - 2) * PX;
-    constexpr int kYoung = (kLoop < kFirst ? kLoop : kFirst) < 63 ? (kLoop < kFirst ? kLoop : kFirst) : 63;
+    constexpr int kYoung = ring_wait_count(CPS, NS, WD, RT, PX, PIPE);
     const int KS = KT / CPS;  // KT is a multiple of CPS
     if constexpr (PIPE) {
         auto read_x = [&](int st, int c, uint4 (&xf)[XG]) {
