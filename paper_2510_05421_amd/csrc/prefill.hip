@@ -206,12 +206,7 @@ __device__ __forceinline__ void swiglu_epilogue(const GemmArgs &a, int t0, int g
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
                 const float gt = acc[t][g][2 * p] * sc[g], up = acc[t][g][2 * p + 1] * sc[g];
-                // bf16 results: the hardware exp2 and reciprocal are within a few ulp of fp32,
-                // 1e-4 of the rounding to bf16 that follows; fp32 results keep expf and division
-                if constexpr (T == DType::BF16)
-                    x[p] = gt * __builtin_amdgcn_rcpf(1.0f + exp_fast(-gt)) * up;
-                else
-                    x[p] = gt / (1.0f + expf(-gt)) * up;
+                x[p] = gt / (1.0f + expf(-gt)) * up;
             }
             if (m < a.M && nt < NT) store_n<T, 2>((E *)a.A + fm_index<T>(m, 8 * nt + 2 * G4, a.N / 2), x);
         }
