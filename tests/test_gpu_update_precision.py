@@ -1,0 +1,56 @@
+"""Sums of the drafter update on inputs where the length of a chain of additions shows.
+
+A sum of one large and many small terms, each below half a unit in the last place of the large one,
+loses every small term that is added to the large one alone, and keeps those that were added up among
+themselves first.  So the error counts the length of the longest chain, and bounds it exactly.
+"""
+import numpy as np
+import pytest
+
+import gpu_util as gu
+import synth
+
+pytestmark = pytest.mark.gpu
+
+BASE = synth.TINY.replace(name="chain", n_layers=1, split_k=1, d_model=48, n_heads=1, n_kv_heads=1, head_dim=64, ffn_dim=32,
+                          vocab=128, lora_rank=16)
+
+
+def _zero_weights(shape):
+    w = synth.make_weights(shape, 0)
+    w.lm_head = np.zeros_like(w.lm_head)
+    w.lora_A, w.lora_B = np.zeros_like(w.lora_A), np.zeros_like(w.lora_B)
+    return w
+
+
+def _update(shape, w, h, a):
+    """Gradients of plain cross-entropy at tokens a (all rows accepted, uniform target logits)."""
+    n = h.shape[0]
+    eng, _ = gu.engine(shape, max_seq=64, weights=w)
+    eng.prefill(synth.make_prompts(shape.vocab, 1, 4, 1))
+    eng.write_buffer(h, a, np.zeros((n, shape.vocab), np.float32), np.ones(n, np.int8), np.ones(n, np.int8))
+    st = eng.update_drafter(0.0, 1.0, 0.0, 0.0, 1.0, 0.0, lr=0.0, grads=True)
+    gA, gB = st["grad_A"].cpu().numpy().astype(np.float64), st["grad_B"].cpu().numpy().astype(np.float64)
+    eng.close()
+    return gA, gB
+
+
+@pytest.mark.parametrize("token", [0, 5, 17, 64, 127])
+def test_du_adds_the_vocabulary_as_a_tree(token):
+    """du = A_s^T g over the 128 vocabulary entries of one workgroup.  The logits are all equal, so g is
+    p - 1 at the token and p = 1/128 elsewhere, and A_s makes the others' products 0.4 units of 2^-24
+    beside one of 127/128 (half a unit there: 2^-25).  A chain of c products with the large one loses
+    0.4 (c - 1) units; in a tree the four products of one MFMA lose 1.2, and each of the seven additions
+    up to du at most half a unit: 4.7, with one unit for g and one for the product with h.  Chains of 32
+    lose 10 to 12."""
+    shape = BASE
+    w = _zero_weights(shape)
+    w.lora_A[:] = -0.4 * 2.0 ** -24 * shape.vocab
+    w.lora_A[token] = 1.0
+    h = np.linspace(0.5, 2.0, shape.d_model).astype(np.float32)[None]
+    _, gB = _update(shape, w, h, np.array([token], np.int32))
+    p = 1.0 / shape.vocab
+    A = w.lora_A.astype(np.float64)
+    du = shape.lora_gamma * (A[token] * (p - 1.0) + p * (A.sum(0) - A[token]))
+    off = np.abs(gB / (du[:, None] * h.astype(np.float64)) - 1.0).max()
+    assert off <= 6.7 * 2.0 ** -24, "%.2f units of 2^-24" % (off * 2.0 ** 24)
