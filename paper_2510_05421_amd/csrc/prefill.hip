@@ -357,19 +357,32 @@ __device__ __forceinline__ void rows_epilogue(const GemmArgs &a, int t0, int g0,
 // ------------------------------------------------------------------------------------------
 constexpr int kStrip = 8;
 
-// The update's logits of up to 64 rows are sums over K in four interleaved parts (chunk mod 4), added
-// at the end: a shorter chain of roundings, as precise as a K split over waves (one chain: 1.5x the
-// error of the updated factors).
+// The update's logits of up to 64 rows, and of any rows in gemm_few_kernel, are sums over K in four
+// interleaved parts (chunk mod 4); every block of chunks the parts are added as a tree and the block's
+// sum to the total, so that no chain of additions is longer than 8 chunks of a part (the ring) or 6
+// (gemm_few_kernel).  The decode GEMM, which had these shapes before, splits K over its waves, in chains
+// of 16 chunks at K = 4096; four parts over all of K were chains of 32, and A_s after an update of 16 rows
+// was 15% further from 64 bits (1.30e-6 -> 1.50e-6).
 constexpr int kUpdateParts = 4;
+constexpr int kRingBlock = 4;  // turns of the ring's weight registers per block (8 chunks each)
 template <int N, int RT, int XG>
-__device__ __forceinline__ void add_parts(f32x4 (&acc)[N][RT][XG]) {
-    static_assert(N == 1 || N == 4, "parts");
-    if constexpr (N == 4)
+__device__ __forceinline__ void zero_parts(f32x4 (&acc)[N][RT][XG]) {
+#pragma unroll
+    for (int q = 0; q < N; ++q)
 #pragma unroll
         for (int t = 0; t < RT; ++t)
 #pragma unroll
-            for (int g = 0; g < XG; ++g)
-                acc[0][t][g] = (acc[0][t][g] + acc[1][t][g]) + (acc[2][t][g] + acc[3][t][g]);
+            for (int g = 0; g < XG; ++g) acc[q][t][g] = (f32x4){0.f, 0.f, 0.f, 0.f};
+}
+template <int N, int RT, int XG>
+__device__ __forceinline__ void fold_parts(f32x4 (&acc)[N][RT][XG], f32x4 (&sum)[1][RT][XG]) {
+    static_assert(N == 4, "parts");
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int g = 0; g < XG; ++g)
+            sum[0][t][g] = sum[0][t][g] + ((acc[0][t][g] + acc[1][t][g]) + (acc[2][t][g] + acc[3][t][g]));
+    zero_parts(acc);
 }
 
 // CPS chunks per stage, NS stages of the ring, WD chunks of weights in flight.
@@ -377,7 +390,7 @@ template <DType T, int EPI, int WV, int RT, int XG, int CPS, int NS, int WD, int
 __global__ void __launch_bounds__(64 * WV, MINW) gemm_rows_kernel(GemmArgs a, int tok_tiles, int blocks, int total) {
     constexpr int PX = CPS * XG / WV;        // copies per wave and stage
     constexpr int UN = WD > CPS ? WD / CPS : 1;  // stages per turn of the weight ring
-    static_assert(PX * WV == CPS * XG && UN * CPS == WD && WD % NACC == 0 && (!PIPE || WD % 2 == 0), "stage and ring shapes");
+    static_assert(PX * WV == CPS * XG && UN * CPS == WD && WD % NACC == 0 && (!PIPE || (WD % 2 == 0 && NACC == 1)), "stage and ring shapes");
     __shared__ __align__(1024) uint4 ring[NS][CPS * XG][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int KT = a.K / ((T == DType::BF16) ? 32 : 16), NT = a.N / 16, NG = (a.M + 15) / 16;
@@ -412,13 +425,9 @@ __global__ void __launch_bounds__(64 * WV, MINW) gemm_rows_kernel(GemmArgs a, in
 #pragma unroll
         for (int t = 0; t < RT; ++t) wf[t] = (wsrc[t] + o)[lane];
     };
-    f32x4 acc[NACC][RT][XG];
-#pragma unroll
-    for (int q = 0; q < NACC; ++q)
-#pragma unroll
-        for (int t = 0; t < RT; ++t)
-#pragma unroll
-            for (int g = 0; g < XG; ++g) acc[q][t][g] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    f32x4 acc[NACC][RT][XG], sum[1][RT][XG];
+    zero_parts(acc);
+    if constexpr (NACC > 1) zero_parts(sum);
 #pragma unroll
     for (int st = 0; st < NS - 1; ++st) copy_stage(st, st);
 #pragma unroll
@@ -501,6 +510,8 @@ __global__ void __launch_bounds__(64 * WV, MINW) gemm_rows_kernel(GemmArgs a, in
                 }
                 st = st + 1 == NS ? 0 : st + 1;
             }
+            if constexpr (NACC > 1)
+                if (s0 / UN % kRingBlock == kRingBlock - 1) fold_parts(acc, sum);  // uniform
         }
     }
     wait_mem<0, true>();  // no copy may land after the workgroup has given its LDS back
@@ -508,8 +519,12 @@ __global__ void __launch_bounds__(64 * WV, MINW) gemm_rows_kernel(GemmArgs a, in
 #pragma unroll
     for (int g = 0; g < XG; ++g)
         sc[g] = a.ss_in != nullptr ? a.sinv_rows[min(16 * (g0 + g) + (lane & 15), a.M - 1)] : 1.0f;
-    add_parts<NACC, RT, XG>(acc);
-    rows_epilogue<T, EPI, RT, XG>(a, t0, g0, acc[0], sc);
+    if constexpr (NACC > 1) {
+        fold_parts(acc, sum);
+        rows_epilogue<T, EPI, RT, XG>(a, t0, g0, sum[0], sc);
+    } else {
+        rows_epilogue<T, EPI, RT, XG>(a, t0, g0, acc[0], sc);
+    }
 }
 
 // Few rows, or few tiles: one wave per feature tile and XG token groups, both operands straight into
@@ -536,11 +551,10 @@ __global__ void __launch_bounds__(64) gemm_few_kernel(GemmArgs a, int gb) {
         for (int g = 0; g < XG; ++g) xf[g] = (xsrc[g] + (size_t)min(k, KT - 1) * 64)[lane];
     };
     constexpr int kAcc = EPI == EPI_LOGITS ? kUpdateParts : 1;
-    f32x4 acc[kAcc][1][XG];
-#pragma unroll
-    for (int q = 0; q < kAcc; ++q)
-#pragma unroll
-        for (int g = 0; g < XG; ++g) acc[q][0][g] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    static_assert(SW % kAcc == 0, "parts of a turn");
+    f32x4 acc[kAcc][1][XG], sum[1][1][XG];
+    zero_parts(acc);
+    if constexpr (kAcc > 1) zero_parts(sum);
 #pragma unroll
     for (int k = 0; k < SW; ++k) load_w(k, w[k]);
 #pragma unroll
@@ -560,6 +574,7 @@ __global__ void __launch_bounds__(64) gemm_few_kernel(GemmArgs a, int gb) {
             load_w(k + SW + i, w[i]);
             load_x(k + SX + i, x[i % SX]);
         }
+        if constexpr (kAcc > 1) fold_parts(acc, sum);
     }
 #pragma unroll
     for (int i = 0; i < SW; ++i)
@@ -568,8 +583,12 @@ __global__ void __launch_bounds__(64) gemm_few_kernel(GemmArgs a, int gb) {
             for (int g = 0; g < XG; ++g) acc[i % kAcc][0][g] = St<T>::mma(w[i], x[i % SX][g], acc[i % kAcc][0][g]);
             load_x(k + SX + i, x[i % SX]);
         }
-    add_parts<kAcc, 1, XG>(acc);
-    rows_epilogue<T, EPI, 1, XG>(a, nt, g0, acc[0], sc);
+    if constexpr (kAcc > 1) {
+        fold_parts(acc, sum);
+        rows_epilogue<T, EPI, 1, XG>(a, nt, g0, sum[0], sc);
+    } else {
+        rows_epilogue<T, EPI, 1, XG>(a, nt, g0, acc[0], sc);
+    }
 }
 
 int compute_units() {

@@ -54,3 +54,31 @@ def test_du_adds_the_vocabulary_as_a_tree(token):
     du = shape.lora_gamma * (A[token] * (p - 1.0) + p * (A.sum(0) - A[token]))
     off = np.abs(gB / (du[:, None] * h.astype(np.float64)) - 1.0).max()
     assert off <= 6.7 * 2.0 ** -24, "%.2f units of 2^-24" % (off * 2.0 ** 24)
+
+
+@pytest.mark.parametrize("vocab,rows", [(1008, 1), (1008, 16), (1008, 40), (1008, 60), (8448, 3), (8448, 33), (8448, 64)])
+def test_logits_of_few_rows_have_no_long_chain(vocab, rows):
+    """The logits' sum over K = 4096 in bf16, 128 chunks of 32 products.  Odd entries of the vocabulary
+    are 16 exactly; even ones have 0.4 units of 2^-20 more per chunk, where one unit is half the spacing
+    of fp32 beside 16.  Their ratio of probabilities shows what was kept: a chain of c chunks onto the 16
+    loses 0.4 (c - 1) units, each addition of partial sums behind it rounds by at most one.  A wave per
+    tile has chains of 6 chunks, two additions that join the parts of a block and one for each of six
+    blocks: 10 units; the ring 8, two and four: 8.8.  Half a unit more for the two exponentials.  Chains
+    of 32 lose 12.4 before the first of these additions."""
+    shape = BASE.replace(d_model=4096, vocab=vocab, lora_rank=4, bf16=True)
+    d = shape.d_model
+    w = _zero_weights(shape)
+    per = synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(np.float32([0.4 * 2.0 ** -20 / 32])))[0]
+    head = np.zeros((vocab, d), np.float32)
+    head[::2] = per
+    head[:, 0] = 16.0
+    w.lm_head = synth.f32_to_bf16_bits(head)
+    w.lora_B[0, 0] = 1.0   # u = 1 for rank 0, A_s = 0: the logits are the head's alone
+    h = np.ones((rows, d), np.float32)
+    tokens = np.arange(rows, dtype=np.int32) * 2 + 1
+    gA, _ = _update(shape, w, h, tokens)
+    free = np.setdiff1d(np.arange(vocab), tokens)
+    gA = gA[free, 0]
+    odd, even = gA[free % 2 == 1], gA[free % 2 == 0]
+    off = np.abs(np.log(even / odd[0]) - float(per) * (d - 1)).max()
+    assert np.ptp(odd) == 0 and off <= 10.5 * 2.0 ** -20, "%.2f units of 2^-20" % (off * 2.0 ** 20)
