@@ -183,6 +183,31 @@ struct AttnArgs {
                          // launches (the merging workgroup resets)
     void *O;             // [M][n_heads*hd] out (dtype, FM)
 };
+// How a decode attention is launched.  LOCAL4 / LOCAL8: at most 4 / 8 chunks, one workgroup of as many
+// waves per (sequence, kv head), partials in LDS.  IN_KERNEL: four chunks a workgroup, the last one to
+// finish merges.  TWO_LAUNCHES: the merge in a launch of its own.  rows: query rows per kv head, heads:
+// n_kv * B, cu: compute units.
+enum AttnRoute { ATTN_LOCAL4, ATTN_LOCAL8, ATTN_IN_KERNEL, ATTN_TWO_LAUNCHES };
+inline AttnRoute attn_route(DType t, int hd, int rows, int n_chunks, long heads, int cu) {
+    // Local, up to 4 chunks: 1.0 to 10 us a launch faster than the chunks split over workgroups at every
+    // type, head dim and number of heads measured (4 to 2560).
+    if (rows <= 16 && n_chunks <= 4) return ATTN_LOCAL4;
+    // Up to 8 chunks: half as many workgroups read the cache, and a wave's chunk is the longer chain in
+    // fp32.  Saved per launch by the one workgroup, at 300 to 505 positions:
+    //   hd 64   bf16: 8 heads 0.0 to 0.4 us, 32 heads 0.5 to 0.6, 64 0.5 to 1.6, 256 and more 2.1 to 5.1
+    //           fp32: 4 to 64 heads -2.0 to -0.8, 128 1.2 to 3.5, 256 and more 2.4 to 6.7
+    //   hd 128  (one workgroup fills a compute unit's LDS, so a last round of few workgroups shows)
+    //           bf16: 32 and 40 heads -0.4 to 1.4 (0.4 on average), 64 to 120 0.2 to 4.7, 128 1.7 to 4.0,
+    //                 160 7.9 to 11, 256 0.9 to 2.8, 320 -0.8 to 1.3, 512 1.0 to 1.7, 640 -1.4 to -0.8,
+    //                 1024 and more 0.2 to 6.8
+    //           fp32: 4 to 64 heads -4.5 to -2.0, 128 -1.8 to 3.6, 256 and more 0.4 to 3.1
+    if (rows <= 16 && n_chunks <= 8) {
+        const bool bf16 = t == DType::BF16;
+        const bool rounds = heads <= cu || heads % cu == 0 || heads >= 4 * (long)cu;
+        if (hd == 64 ? bf16 || 2 * heads >= cu : (bf16 ? 8 * heads >= cu : heads >= cu) && rounds) return ATTN_LOCAL8;
+    }
+    return n_chunks * heads >= 1024 || rows > 4 ? ATTN_TWO_LAUNCHES : ATTN_IN_KERNEL;
+}
 // Merge counters sit 256 bytes apart: every chunk workgroup of a (sequence, kv head) takes its
 // counter once, and counters sharing a line would serialise all heads' updates in one place.
 constexpr int kCounterStride = 64;

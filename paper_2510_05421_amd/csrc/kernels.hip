@@ -674,8 +674,6 @@ __device__ __forceinline__ void merge_row(const AttnArgs &a, int m, int h, int n
     store_row<T, HD>(a, m, h, lane, o, L);
 }
 
-constexpr long kAttnLargeGrid = 1024;  // chunk-waves from which the merge takes its own launch
-
 // One wave's 64-key chunk ch of (sequence b, kv head kvh), nk of its keys in the cache.
 // Keys are cut into 64-position chunks at absolute positions; the query rows that read this kv
 // head (c tokens x n_heads/n_kv grouped heads) are taken 16 at a time as the MFMA row dimension:
@@ -1053,22 +1051,13 @@ static void launch_attention_t(const AttnArgs &a, hipStream_t s, const LaunchEve
     // otherwise every workgroup would wait for its partial stores before counting itself done,
     // and the last merges would run at the kernel's tail, each wave merging several rows one
     // after another (6 rows: 17.1 -> 16.0 us, 20 rows: 18.6 -> 15.7 us with the second launch).
-    // The large grid starts at 1024 chunk-waves: four 7B sequences of 440-700 positions (1536) step in
-    // 549 us with the second launch against 588, one 13B sequence of 1024 (800) in 2538 against 2531,
-    // one 7B sequence of 512 (384) the same either way.
     const int rows = a.c * (a.n_heads / a.n_kv);
-    // Contexts of up to 256 and 512 positions with one query tile stay in one workgroup per head (tiny
-    // fp32 step of four sequences 462 -> 450 us, 1B step at 260 positions 2606 -> 2597 us).
-    if (rows <= 16 && a.n_chunks <= 4) {
+    const AttnRoute route = attn_route(T, HD, rows, a.n_chunks, (long)a.n_kv * a.B, compute_units());
+    if (route == ATTN_LOCAL4) {
         launch_timed(attn_local_kernel<T, HD, 4>, dim3(a.n_kv, a.B), dim3(256), s, ev, a);
-        return;
-    }
-    if (rows <= 16 && a.n_chunks <= 8) {
+    } else if (route == ATTN_LOCAL8) {
         launch_timed(attn_local_kernel<T, HD, 8>, dim3(a.n_kv, a.B), dim3(512), s, ev, a);
-        return;
-    }
-    const long waves = (long)a.n_chunks * a.n_kv * a.B;
-    if (waves >= kAttnLargeGrid || rows > 4) {
+    } else if (route == ATTN_TWO_LAUNCHES) {
         const int all_rows = a.B * a.c * a.n_heads;
         LaunchEvents e1 = ev, e2 = ev;  // one interval around both launches
         e1.stop = nullptr;
