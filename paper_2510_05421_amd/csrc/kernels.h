@@ -206,7 +206,14 @@ inline AttnRoute attn_route(DType t, int hd, int rows, int n_chunks, long heads,
         const bool rounds = heads <= cu || heads % cu == 0 || heads >= 4 * (long)cu;
         if (hd == 64 ? bf16 || 2 * heads >= cu : (bf16 ? 8 * heads >= cu : heads >= cu) && rounds) return ATTN_LOCAL8;
     }
-    return n_chunks * heads >= 1024 || rows > 4 ? ATTN_TWO_LAUNCHES : ATTN_IN_KERNEL;
+    // The last workgroup can merge up to four rows, one a wave.  That saves a launch as long as all
+    // workgroups run at once: saved per launch by the second launch
+    //   up to 960 chunk-waves (240 workgroups)   -1.9 to 0.3 us
+    //   1024 (one a compute unit)                32 chunks a row -1.6 to 0.4, 8 and 16 -0.4 to 4.1
+    //   1280 and more                            2.0 to 47
+    const long wgs = (long)((n_chunks + 3) / 4) * heads;
+    if (rows > 4 || wgs > cu || (wgs == cu && n_chunks <= 16)) return ATTN_TWO_LAUNCHES;
+    return ATTN_IN_KERNEL;
 }
 // Merge counters sit 256 bytes apart: every chunk workgroup of a (sequence, kv head) takes its
 // counter once, and counters sharing a line would serialise all heads' updates in one place.

@@ -1047,7 +1047,7 @@ static void launch_attention_t(const AttnArgs &a, hipStream_t s, const LaunchEve
     // 1.478 ms with one query row per kv head, against 1.468 ms with the ordering left to cache
     // policy bits (a relaxed counter), which the memory model does not guarantee.  A large grid, or
     // more query rows per kv head than the last workgroup has waves (verify blocks of 6 or more,
-    // grouped-head verify, prefill blocks), merges in a second launch instead, one wave per row:
+    // grouped-head verify), merges in a second launch instead, one wave per row:
     // otherwise every workgroup would wait for its partial stores before counting itself done,
     // and the last merges would run at the kernel's tail, each wave merging several rows one
     // after another (6 rows: 17.1 -> 16.0 us, 20 rows: 18.6 -> 15.7 us with the second launch).

@@ -25,6 +25,9 @@ int main() {
         {H, 128, 1, 8, 2560, L8},
         // more than 4 query rows with more than 8 chunks, more than 16 rows
         {H, 128, 6, 12, 32, K2}, {F, 64, 8, 12, 4, K2}, {H, 128, 24, 4, 32, K2}, {H, 64, 32, 8, 8, K2},
+        // one workgroup a compute unit, and just above
+        {H, 128, 1, 32, 32, K1}, {H, 128, 4, 32, 32, K1 | K2}, {H, 64, 1, 32, 32, K1 | K2}, {F, 64, 1, 32, 32, K1}, {F, 128, 1, 32, 32, K1},
+        {H, 64, 4, 16, 64, K2}, {F, 128, 4, 16, 64, K2}, {F, 128, 4, 8, 128, K2}, {H, 128, 1, 32, 40, K2}, {H, 128, 4, 32, 40, K2},
         // more than 8 chunks: clear on both sides of the line
         {H, 128, 1, 12, 32, K1}, {H, 128, 1, 16, 40, K1}, {H, 64, 1, 24, 32, K1}, {H, 64, 4, 32, 8, K1}, {F, 64, 1, 32, 4, K1},
         {F, 64, 1, 24, 32, K1}, {F, 128, 1, 32, 16, K1}, {H, 128, 1, 12, 128, K2}, {H, 128, 1, 32, 64, K2}, {F, 64, 1, 12, 128, K2},
