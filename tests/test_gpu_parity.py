@@ -219,12 +219,14 @@ def test_buffer_rows_hold_the_verify_logits_and_normed_states():
                                                 ("tiny", 300, 64, None), ("tiny", 100, 16, 4112),
                                                 ("tiny", 64, 16, 33024)])
 def test_drafter_update_gradients_match_oracle(name, n_rows, r, vocab):
-    """Row counts cover the update GEMM's 4-, 8- and 16-group variants and more rows than one
-    launch takes (300 > 256).  Ranks other than 16 take the large-M logits epilogue through one
-    partial pass over the rank (20), two passes (40: 32 + 8) and two full passes (64).  A
-    vocabulary of 4112 = 32 * 128 + 16 leaves the gradient pass's last 128-entry block mostly
-    empty; one of 33024 = 32 * 1024 + 256 sends the row kernel past the 32 entries per thread it
-    holds in registers."""
+    """On 256 compute units the logits GEMM runs a wave per 16-entry tile for up to 100 rows of the tiny
+    shape's 4096 entries, 64 x 64 tiles for 300 rows and for 64 rows of 33024 entries, 128 x 256 tiles for
+    the 1B shape.  Ranks other than 16 take the LoRA term and the
+    gradients of A_s and du in passes of 16 ranks, the last one partly empty (20: 16 + 4, 40: 16 + 16 + 8) or
+    full (64).  300 rows leave the last 16-row block of the gradient pass and the last 256-row block of dB
+    partly empty.  A vocabulary of 4112 = 32 * 128 + 16 leaves the gradient pass's last 128-entry block mostly
+    empty; one of 33024 = 32 * 1024 + 256 sends the row kernel past the 32 entries per thread it holds in
+    registers."""
     shape = gu.SHAPES[name].replace(lora_rank=r)
     if vocab is not None:
         shape = shape.replace(vocab=vocab)

@@ -68,15 +68,32 @@ def test_ragged_prefill_equals_single_sequences(name, lens):
             gu.check_close(logits[b], ref.logits[0], shape, "sequence %d" % b)
 
 
-@pytest.mark.parametrize("name,rows,r", [("odd", 1, 16), ("odd", 16, 3), ("odd", 17, 16), ("odd", 65, 1), ("odd", 256, 3),
-                                         ("wide", 48, 16), ("wide", 64, 3), ("fp32", 33, 18), ("fp32", 130, 16)])
-def test_update_logits_launch_shapes(name, rows, r):
-    """The drafter update's logits GEMM over the same launch shapes, with ranks that are not a multiple
-    of four among them.  The engine sums fp32 products of the oracle's own inputs (a few hundred
-    terms, 6e-8 each): 1e-4 leaves two orders."""
+UPDATES = [
+    # a wave per tile: one to four token groups
+    ("odd", 1, 16, 1008), ("odd", 16, 3, 1008), ("odd", 17, 16, 1008), ("odd", 65, 1, 1008), ("odd", 256, 3, 1008),
+    ("wide", 48, 16, 1008), ("wide", 64, 3, 1008), ("fp32", 33, 18, 1008), ("fp32", 130, 16, 1008),
+    # 64 x 64 tiles: up to 64 rows, four parts of K; more rows of a narrower matrix, one
+    ("wide", 48, 16, 32016), ("wide", 64, 3, 32016), ("fp32_128", 48, 16, 32016), ("wide", 80, 16, 8464),
+    # 64 x 128 tiles: four-chunk and two-chunk stages
+    ("wide", 160, 16, 8464), ("wide10", 160, 3, 8464),
+    # 128 x 128 tiles: more and fewer workgroups than compute units
+    ("wide", 400, 16, 8464), ("wide", 128, 16, 32016), ("fp32_128", 100, 3, 32016),
+    # 128 x 256 tiles: eight waves, four waves
+    ("wide", 200, 18, 32016), ("fp32_128", 130, 3, 32016), ("wide", 300, 3, 32016), ("fp32_128", 300, 16, 32016),
+    # one-chunk stages
+    ("odd", 100, 16, 32016), ("odd", 300, 3, 32016), ("fp32", 100, 16, 32016),
+]
+
+
+@pytest.mark.parametrize("name,rows,r,vocab", UPDATES)
+def test_update_logits_launch_shapes(name, rows, r, vocab):
+    """The drafter update's logits GEMM in each of its launch shapes on 256 compute units, with ranks that
+    are not a multiple of four and vocabularies that leave the last tiles partly empty among them.  The
+    engine sums fp32 products of the oracle's own inputs (a few hundred terms, 6e-8 each): 1e-4 leaves two
+    orders."""
     from oracle import update as oupd
-    shape = SHAPES[name].replace(lora_rank=r)
-    eng, w = gu.engine(shape, max_seq=64, lora_A_std=0.02)
+    shape = SHAPES[name].replace(lora_rank=r, vocab=vocab)
+    eng, w = gu.engine(shape, max_seq=64, lora_A_std=0.02, buffer_rows=max(256, rows))
     buf = synth.make_buffer(shape.d_model, shape.vocab, rows, seed=11)
     eng.prefill(synth.make_prompts(shape.vocab, 1, 8, 1))
     eng.write_buffer(buf.h, buf.a, buf.logits, buf.r, buf.fresh)
