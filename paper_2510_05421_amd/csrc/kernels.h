@@ -46,6 +46,18 @@ struct PackSrc {
 };
 void launch_pack(DType t, PackSrc srcs, const int32_t *prow_dev, int N, int K, void *dst, hipStream_t s);
 
+// Compute units of the device (of the one current at the first call).
+inline int compute_units() {
+    static const int cu = [] {
+        int dev = 0, v = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0)
+            v = 256;
+        return v;
+    }();
+    return cu;
+}
+
 enum Epi : int {
     EPI_RESID = 0,   // H[m][n] += y                          (attention out, MLP down)
     EPI_QKV = 1,     // rotary embed q,k; q -> Q[m]; k,v -> KV cache at the token's position
@@ -118,8 +130,9 @@ struct LaunchEvents {
 // independent of M.
 bool launch_gemm(DType t, Epi e, const GemmArgs &a, hipStream_t s, const LaunchEvents &ev = {});
 // The many-row GEMM, any M (prefill blocks; the drafter update's logits, EPI_LOGITS with the LoRA term
-// and neither argmax partials nor sampling).  Its arithmetic per output is independent of M too, but
-// not the decode GEMM's.
+// and neither argmax partials nor sampling).  Its arithmetic per output is not the decode GEMM's; for
+// the prefill epilogues it is independent of M too, for EPI_LOGITS it is not (K in one chain or in parts,
+// by rows, vocabulary and compute units).
 void launch_gemm_rows(DType t, Epi e, const GemmArgs &a, hipStream_t s, const LaunchEvents &ev = {});
 // Bytes of GemmArgs::kpart for an N x K matrix (64 tokens); 0 when that matrix never splits.
 size_t gemm_split_bytes(DType t, int N, int K);

@@ -1,11 +1,11 @@
 // gfx950 (CDNA4) kernels for the DVI self-speculative decode step.
 //
-// Every reduction here has a fixed order that depends only on the operand shape (K, head
-// dim, vocabulary, chunk size), never on how many tokens are processed together.  Any
-// token's result is therefore the same whether it is computed alone (one draft token),
-// inside a verify block, or inside a prefill chunk: that is what makes the committed keys
-// and values bitwise independent of which drafts were proposed, and the speculative output
-// identical to plain greedy decoding on the same engine.
+// Every reduction of the decode step has a fixed order that depends only on the operand shape
+// (K, head dim, vocabulary, chunk size), never on how many tokens are processed together.  Any
+// token's result is therefore the same whether it is computed alone (one draft token) or inside
+// a verify block: that is what makes the committed keys and values bitwise independent of which
+// drafts were proposed, and the speculative output identical to plain greedy decoding on the
+// same engine.  (Prompt tokens always go through the kernels of prefill.hip, in both runs.)
 #include "kernels.h"
 
 #include <hip/hip_ext.h>
@@ -322,16 +322,6 @@ __global__ void __launch_bounds__(256) gemm_fold_kernel(GemmArgs a, int mg) {
 struct GemmShape {
     int rt, waves;
 };
-static int compute_units() {
-    static const int cu = [] {
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0)
-            v = 256;
-        return v;
-    }();
-    return cu;
-}
 static GemmShape gemm_shape(int N, int K, int KC, int M) {
     const int tiles = N / 16, chunks = K / KC, mg = (M + 15) / 16;
     // K split, from the matrix only: the most waves per workgroup (up to 16) that keep the whole
@@ -848,7 +838,7 @@ struct AttnTile {
     }
 };
 
-// Any number of query tiles (prefill blocks): the first query tile and the chunk's key and
+// Any number of query tiles (grouped heads): the first query tile and the chunk's key and
 // value fragments are all requested before any of them is used; further tiles follow one by one.
 template <DType T, int HD, typename Sink>
 __device__ __forceinline__ void attn_chunk(const AttnArgs &a, int b, int kvh, int ch, int len0, int nk,
@@ -864,7 +854,7 @@ __device__ __forceinline__ void attn_chunk(const AttnArgs &a, int b, int kvh, in
     // keep every load above in flight before the first use of any of them
     __builtin_amdgcn_sched_barrier(0);
     for (int r0 = 0; r0 < R; r0 += 16) {
-        // a tile whose last row sits before this chunk has no keys here (prefill blocks)
+        // a tile whose last row sits before this chunk has no keys here (a block over a chunk's edge)
         if (len0 + min(R - 1, r0 + 15) / G < ch * CK) continue;  // uniform across the wave
         if (r0 > 0) A::load_q(a, b, kvh, r0, qraw);
         uint4 qf[A::DS];

@@ -1,11 +1,13 @@
 // gfx950 kernels of the many-row passes: prefill blocks (row embedding, GEMMs, causal attention) and
 // the drafter update's logits GEMM.
 //
-// Every output's arithmetic is fixed by the matrix and the row alone: a GEMM output accumulates its
-// K chunks in increasing order, one MFMA per chunk, whatever tile, wave or launch shape it sits in,
-// and a query row's softmax runs over its 64-key chunks in increasing order.  A prompt's keys,
-// values and logits therefore do not depend on its batch, on how its rows are cut into blocks or on
-// the launch shape chosen for them.
+// Every output of a prefill block has its arithmetic fixed by the matrix and the row alone: a GEMM output
+// accumulates its K chunks in increasing order, one MFMA per chunk, whatever tile, wave or launch shape
+// it sits in, and a query row's softmax runs over its 64-key chunks in increasing order.  A prompt's
+// keys, values and logits therefore do not depend on its batch, on how its rows are cut into blocks or
+// on the launch shape chosen for them.  The update's logits (EPI_LOGITS) make no such promise: where few
+// rows or few tiles select it, K is summed in parts (kUpdateParts), elsewhere in one chain, so a replay
+// row's last bits depend on how many rows the ring holds and on the number of compute units.
 #include "kernels.h"
 
 #include <hip/hip_ext.h>
@@ -46,8 +48,8 @@ __device__ __forceinline__ float sumsq4(float a, float b, float c, float d) {
 // Row m of the block is row t0 + m of the prompts laid end to end: sequence b with starts[b] <= t <
 // starts[b + 1], position t - starts[b].  rowmap[m] = (b, position); h = E[token] (fp32), its partial
 // sums of squares per 16 columns, and hg = dtype(h * g) (FM) for the first layer's folded RMSNorm.
-// Bound by the stores (14 bytes per element in bf16): every thread holds EPL consecutive columns, so
-// loads and stores are 16 bytes wide (2048 rows of the 7B shape: 60 us with 2-byte accesses).
+// Bound by the stores (h and hg, 6 bytes per element in bf16): every thread holds EPL consecutive columns,
+// so loads and stores are 16 bytes wide (2048 rows of the 7B shape: 60 us with 2-byte accesses).
 template <DType T>
 __global__ void __launch_bounds__(256) embed_rows_kernel(const void *emb, const int32_t *ids, const int32_t *starts,
                                                          int B, int t0, int d, float *h, float *ss, void *hg,
@@ -137,8 +139,9 @@ __global__ void __launch_bounds__(64) rms_rows_kernel(const float *ss, int ld_ss
 // Epilogues.  A wave holds tiles t0 .. t0 + RT - 1 (16 features each) of token groups g0 .. g0 + XG - 1
 // in the MFMA output layout: acc[t][g][j] is feature 16 (t0 + t) + 4 (l / 16) + j of token 16 (g0 + g)
 // + l % 16.  The same operations per output as the decode GEMM's epilogue; the operands of the next
-// token group are requested while one is computed, and every store is as wide as the layout allows
-// (8 x 2048 prefill, 7B: the K = 4096 GEMMs spent 24-48 us per tile round in per-element epilogues).
+// token group are requested while one is computed, and every store is as wide as a lane's values lie
+// together: 16, 8 or 4 bytes, but one element in the value cache, which runs along the tokens (8 x 2048
+// prefill, 7B: the K = 4096 GEMMs spent 24-48 us per tile round in per-element epilogues).
 // sc[g]: 1/rms of the lane's token.
 // ------------------------------------------------------------------------------------------
 template <DType T, int N>
@@ -589,17 +592,6 @@ __global__ void __launch_bounds__(64) gemm_few_kernel(GemmArgs a, int gb) {
     } else {
         rows_epilogue<T, EPI, 1, XG>(a, nt, g0, acc[0], sc);
     }
-}
-
-int compute_units() {
-    static const int cu = [] {
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0)
-            v = 256;
-        return v;
-    }();
-    return cu;
 }
 
 template <typename... P, typename... Q>
