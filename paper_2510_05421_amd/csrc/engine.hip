@@ -1228,6 +1228,18 @@ extern "C" dvi_status dvi_abort_step(dvi_ctx *x) {
 // ------------------------------------------------------------------------------------------
 // C ABI: drafter update
 // ------------------------------------------------------------------------------------------
+// Whether a kernel may store to p: memory of the context's own device.  Another GPU's memory is reached by
+// a copy (a store without peer access faults).
+static bool own_memory(const dvi_ctx *x, const void *p) {
+    hipPointerAttribute_t at{};
+    if (p == nullptr) return false;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == x->dev;
+}
+
 extern "C" dvi_status dvi_update_drafter(dvi_ctx *x, const dvi_update_args *ua, dvi_update_stats *stats) {
     if (!x || !ua) return DVI_ERR_ARG;
     if (x->device_error) return fail(x, DVI_ERR_DEVICE, "context has a sticky device error");
@@ -1274,8 +1286,12 @@ extern "C" dvi_status dvi_update_drafter(dvi_ctx *x, const dvi_update_args *ua, 
     FinishArgs f{};
     f.gA = x->upd_dA;
     f.gB = x->upd_dB;
-    f.outA = ua->grad_A_out;
-    f.outB = ua->grad_B_out;
+    f.outA = own_memory(x, ua->grad_A_out) ? ua->grad_A_out : nullptr;
+    f.outB = own_memory(x, ua->grad_B_out) ? ua->grad_B_out : nullptr;
+    if (ua->grad_A_out && !f.outA)
+        HIPCHK(x, hipMemcpyAsync(ua->grad_A_out, x->upd_dA, nA * 4, hipMemcpyDeviceToDevice, x->stream));
+    if (ua->grad_B_out && !f.outB)
+        HIPCHK(x, hipMemcpyAsync(ua->grad_B_out, x->upd_dB, nB * 4, hipMemcpyDeviceToDevice, x->stream));
     f.A = x->lora_A;
     f.B = x->lora_B;
     f.mA = x->mA;

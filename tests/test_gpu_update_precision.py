@@ -82,3 +82,31 @@ def test_logits_of_few_rows_have_no_long_chain(vocab, rows):
     odd, even = gA[free % 2 == 1], gA[free % 2 == 0]
     off = np.abs(np.log(even / odd[0]) - float(per) * (d - 1)).max()
     assert np.ptp(odd) == 0 and off <= 10.5 * 2.0 ** -20, "%.2f units of 2^-20" % (off * 2.0 ** 20)
+
+
+def test_gradients_into_memory_that_is_not_the_devices_own():
+    """Gradient buffers outside the context's device memory (here pinned host memory) are filled by a
+    copy, with the same values as buffers on the device."""
+    import ctypes
+
+    import torch
+    from paper_2510_05421_amd import _abi
+    shape = BASE.replace(vocab=1008)
+    eng, w = gu.engine(shape, max_seq=64, lora_A_std=0.02)
+    buf = synth.make_buffer(shape.d_model, shape.vocab, 20, seed=11)
+    eng.prefill(synth.make_prompts(shape.vocab, 1, 4, 1))
+    got = []
+    for where in ("device", "pinned", "mixed"):
+        eng.write_buffer(buf.h, buf.a, buf.logits, buf.r, buf.fresh)
+        torch.cuda.synchronize()
+        gA = torch.zeros(shape.vocab, shape.lora_rank, pin_memory=True) if where == "pinned" else torch.zeros_like(eng.lora_A)
+        gB = torch.zeros_like(eng.lora_B) if where == "device" else torch.zeros(shape.lora_rank, shape.d_model, pin_memory=True)
+        torch.cuda.synchronize()
+        args = _abi.UpdateArgs(0.7, 0.9, 0.4, 0.05, 1.3, 0.35, 0.0, 0.9, 0.999, 1e-8, 0, gA.data_ptr(), gB.data_ptr())
+        assert eng.lib.dvi_update_drafter(eng.ctx, ctypes.byref(args), None) == _abi.OK
+        torch.cuda.synchronize()
+        got.append((gA.cpu().numpy().copy(), gB.cpu().numpy().copy()))
+    eng.close()
+    assert got[0][0].any() and got[0][1].any()
+    for a, b in got[1:]:
+        assert np.array_equal(a, got[0][0]) and np.array_equal(b, got[0][1])
