@@ -38,8 +38,9 @@ KERNEL_NAMES = {"gate_up": "gemm_kernel<bf16,MG=1,EPI_SWIGLU> (gate/up projectio
 # (FETCH_SIZE, WRITE_SIZE) over this benchmark, scaled by what the same counters read for a
 # plain device copy.  Used only while the kernel source it was taken on is unchanged.
 TRAFFIC_PROFILES = {"gate_up": "profiles/gemm_gate_up_7b_b1_k4_traffic.md"}
-# the device code of every kernel: a counter summary stands only while these are unchanged
-KERNEL_SOURCES = ("paper_2510_05421_amd/csrc/kernels.hip", "paper_2510_05421_amd/csrc/device.h")
+# the device code of every kernel and the launch rules: a counter summary stands only while these are unchanged
+KERNEL_SOURCES = tuple("paper_2510_05421_amd/csrc/" + f
+                       for f in ("kernels.hip", "prefill.hip", "device.h", "kernels.h", "ring.h"))
 
 
 def kernel_sources_sha256():
