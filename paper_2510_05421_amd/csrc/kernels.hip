@@ -1463,8 +1463,8 @@ __device__ __forceinline__ void stage_rank_slice(float (&dst)[256][16], const fl
 // wave keeps its dA sums over its blocks (the eight waves are added in order through LDS); a block's
 // du sums go to du_part[b][i][16], and upd_du_sum_kernel adds the workgroups' shares.  V is a multiple
 // of 16, as every vocabulary here.  Bound by the latency of one block's loads and then by memory; with
-// vector fmas and a 64-lane reduction per row it was bound by those: 256 rows of V = 32000 28.9 -> 18.3 us
-// (the whole update, at d = 5120, 258 -> 247), 48 rows 14.1 -> 12.3.
+// vector fmas and a 64-lane reduction per row it was bound by those: 256 rows of V = 32000 28.9 -> 19.5 us
+// (the whole update, at d = 5120, 258 -> 249), 48 rows 14.1 -> 12.4.
 constexpr int kGradWaves = 8;
 
 __global__ void __launch_bounds__(64 * kGradWaves) upd_grad_kernel(UpdateArgs u, int c0) {

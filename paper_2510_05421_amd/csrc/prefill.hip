@@ -351,8 +351,8 @@ __device__ __forceinline__ void rows_epilogue(const GemmArgs &a, int t0, int g0,
 // 8192 rows, in sequence and so at the clock this load settles at: gate/up 1212 -> 1189 us, QKV 778 ->
 // 741, out-proj and down 985 -> 929 against eight waves of two feature tiles without PIPE; 512 rows: QKV
 // 78 -> 73, out-proj and down 128 -> 117.  256 x 256 tiles (1254, 769, 968 us) and more bytes in flight
-// change little, and at 1240 TFLOP/s little is left (the library's 8192 cubed
-// product reaches 1470).
+// change little.  Gate/up takes 1211 us with expf and a division in its epilogue, 1220 TFLOP/s (the
+// library's 8192 cubed product reaches 1470).
 // Workgroups are numbered so that each XCD (workgroup id mod 8) takes a contiguous range of tiles,
 // in strips of kStrip feature blocks with the token tile major: the tiles that run together on an
 // XCD form a near-square, which reads the fewest bytes into its L2 (gate/up, 8192 rows: 1167 ->
