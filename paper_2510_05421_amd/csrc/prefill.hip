@@ -366,6 +366,12 @@ constexpr int kStrip = 8;
 // (gemm_few_kernel).  The decode GEMM, which had these shapes before, splits K over its waves, in chains
 // of 16 chunks at K = 4096; four parts over all of K were chains of 32, and A_s after an update of 16 rows
 // was 15% further from 64 bits (1.30e-6 -> 1.50e-6).
+// Where one token tile covers the rows, these launches read every weight once, non-temporally, as the
+// decode GEMM does: between two updates the decode steps have streamed gigabytes, and ordinary loads of a
+// head that is not in the last-level cache cost 20 to 50 us more and leave nothing of the ring's rows
+// there.  An update at V = 32000, d = 4096 with cold caches: 8 rows 212 -> 170 us (172 with the decode
+// GEMM), 48 rows 219 -> 179 (225); with the head still cached from the update before 159 -> 161 and 169 ->
+// 172.
 constexpr int kUpdateParts = 4;
 constexpr int kRingBlock = 4;  // turns of the ring's weight registers per block (8 chunks each)
 template <int N, int RT, int XG>
@@ -426,7 +432,7 @@ __global__ void __launch_bounds__(64 * WV, MINW) gemm_rows_kernel(GemmArgs a, in
     auto load_w = [&](int k, uint4 (&wf)[RT]) {
         const size_t o = (size_t)min(k, KT - 1) * 64;
 #pragma unroll
-        for (int t = 0; t < RT; ++t) wf[t] = (wsrc[t] + o)[lane];
+        for (int t = 0; t < RT; ++t) wf[t] = NACC > 1 ? ld_stream(wsrc[t] + o + lane) : (wsrc[t] + o)[lane];
     };
     f32x4 acc[NACC][RT][XG], sum[1][RT][XG];
     zero_parts(acc);
@@ -536,7 +542,7 @@ __global__ void __launch_bounds__(64 * WV, MINW) gemm_rows_kernel(GemmArgs a, in
 // one compute unit can stream (about 50 GB/s of cold lines).  1/rms of the tokens is computed here,
 // under the operand stream.  1B shapes, 37 rows, against the LDS-staged kernel before (16 workgroups
 // for 2048 features): out-proj 38 -> 8 us, down 120 -> 17, QKV 41 -> 9.
-template <DType T, int EPI, int XG, int SW, int SX>
+template <DType T, int EPI, int XG, int SW, int SX, bool ONCE>
 __global__ void __launch_bounds__(64) gemm_few_kernel(GemmArgs a, int gb) {
     static_assert(SW % SX == 0, "ring depths");
     const int lane = threadIdx.x;
@@ -548,7 +554,10 @@ __global__ void __launch_bounds__(64) gemm_few_kernel(GemmArgs a, int gb) {
 #pragma unroll
     for (int g = 0; g < XG; ++g) xsrc[g] = (const uint4 *)a.X + (size_t)min(g0 + g, NG - 1) * KT * 64;
     uint4 w[SW], x[SX][XG];
-    auto load_w = [&](int k, uint4 &wf) { wf = (wsrc + (size_t)min(k, KT - 1) * 64)[lane]; };
+    auto load_w = [&](int k, uint4 &wf) {
+        const uint4 *p = wsrc + (size_t)min(k, KT - 1) * 64 + lane;
+        wf = ONCE ? ld_stream(p) : *p;
+    };
     auto load_x = [&](int k, uint4 (&xf)[XG]) {
 #pragma unroll
         for (int g = 0; g < XG; ++g) xf[g] = (xsrc[g] + (size_t)min(k, KT - 1) * 64)[lane];
@@ -611,10 +620,10 @@ void launch_rows(const GemmArgs &a, hipStream_t s, const LaunchEvents &ev) {
               s, ev, a, tok, blk, total);
 }
 
-template <DType T, int EPI, int XG, int SW, int SX>
+template <DType T, int EPI, int XG, int SW, int SX, bool ONCE = false>
 void launch_few(const GemmArgs &a, hipStream_t s, const LaunchEvents &ev) {
     const int NT = a.N / 16, gb = ((a.M + 15) / 16 + XG - 1) / XG;
-    launch_ev(gemm_few_kernel<T, EPI, XG, SW, SX>, dim3((NT + 7) / 8 * 8 * gb), dim3(64), s, ev, a, gb);
+    launch_ev(gemm_few_kernel<T, EPI, XG, SW, SX, ONCE>, dim3((NT + 7) / 8 * 8 * gb), dim3(64), s, ev, a, gb);
 }
 
 // Launch shape (times: weights cold, as inside a model).
@@ -639,7 +648,7 @@ void gemm_rows_t(const GemmArgs &a, hipStream_t s, const LaunchEvents &ev) {
     constexpr int NACC = EPI == EPI_LOGITS ? kUpdateParts : 1;
     const long want = (long)cu * 3 / 4;
     auto wgs = [&](int rows, int feats) { return (long)((a.M + rows - 1) / rows) * ((a.N + feats - 1) / feats); };
-    if (NG == 1) return launch_few<T, EPI, 1, 24, 12>(a, s, ev);
+    if (NG == 1) return launch_few<T, EPI, 1, 24, 12, EPI == EPI_LOGITS>(a, s, ev);
     if (a.M <= 64 && NT > 2 * cu && KT % 2 == 0) return launch_rows<T, EPI, 4, 1, 4, 2, 4, 8, 2, false, NACC>(a, s, ev);
     if (a.M <= 64 || wgs(64, 64) < want) {
         const int xg = (int)std::min<long>(4, std::max<long>(1, (long)NT * NG / cu));
